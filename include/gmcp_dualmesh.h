@@ -39,6 +39,16 @@ extern "C" {
 int gmcp_dualmesh_embed(const double *P, int64_t N, const double *V, const int32_t *F, int64_t nT, int32_t *tri,
                         double *bary, double *delta, double *dist2, void *stream);
 
+/* The same mapping with scratch memory: work (device, at least
+ * gmcp_dualmesh_embed_work_bytes(N, nT) bytes, else GMCP_E_ARG; free to
+ * reuse once the stream has passed the call) lets the search walk a tree
+ * over the triangles instead of scanning all of them.  The results are those
+ * of gmcp_dualmesh_embed.  A size of 0 bytes means that the scan is used
+ * (few triangles); work may then be NULL. */
+size_t gmcp_dualmesh_embed_work_bytes(int64_t N, int64_t nT);
+int gmcp_dualmesh_embed_ws(const double *P, int64_t N, const double *V, const int32_t *F, int64_t nT, int32_t *tri,
+                           double *bary, double *delta, double *dist2, void *work, size_t work_bytes, void *stream);
+
 /* out [N][3] = Eq. (bary_interp) on the deformed simulation positions
  * Vd [nV][3].  flags & GMCP_F64 (1): Vd, bary, delta and out are double;
  * otherwise float. */

@@ -65,7 +65,8 @@ FEM_EXPORTS = ["gmcp_fem_workspace_size", "gmcp_fem_create", "gmcp_fem_destroy",
                "gmcp_fem_nnzb", "gmcp_fem_stiffness", "gmcp_fem_energy", "gmcp_fem_apply", "gmcp_fem_solve"]
 
 # include/gmcp_dualmesh.h
-DUALMESH_EXPORTS = ["gmcp_dualmesh_embed", "gmcp_dualmesh_update"]
+DUALMESH_EXPORTS = ["gmcp_dualmesh_embed", "gmcp_dualmesh_embed_work_bytes", "gmcp_dualmesh_embed_ws",
+                    "gmcp_dualmesh_update"]
 
 _lib = None
 

@@ -21,6 +21,10 @@ def _lib():
         P = C.c_void_p
         L.gmcp_dualmesh_embed.restype = C.c_int
         L.gmcp_dualmesh_embed.argtypes = [P, C.c_int64, P, P, C.c_int64, P, P, P, P, P]
+        L.gmcp_dualmesh_embed_work_bytes.restype = C.c_size_t
+        L.gmcp_dualmesh_embed_work_bytes.argtypes = [C.c_int64, C.c_int64]
+        L.gmcp_dualmesh_embed_ws.restype = C.c_int
+        L.gmcp_dualmesh_embed_ws.argtypes = [P, C.c_int64, P, P, C.c_int64, P, P, P, P, P, C.c_size_t, P]
         L.gmcp_dualmesh_update.restype = C.c_int
         L.gmcp_dualmesh_update.argtypes = [P, P, P, P, P, C.c_int64, P, C.c_uint32, P]
         L._dualmesh_typed = True
@@ -49,9 +53,11 @@ class DualMesh:
         bary = torch.empty(self.N, 3, dtype=torch.float64, device=dev)
         delta = torch.empty(self.N, dtype=torch.float64, device=dev)
         self.dist2 = torch.empty(self.N, dtype=torch.float64, device=dev)
-        _check(_lib().gmcp_dualmesh_embed(_ptr(P), self.N, _ptr(V), _ptr(self.F), self.F.shape[0], _ptr(self.tri),
-                                          _ptr(bary), _ptr(delta), _ptr(self.dist2), _stream(dev)),
-               "gmcp_dualmesh_embed")
+        nbytes = int(_lib().gmcp_dualmesh_embed_work_bytes(self.N, self.F.shape[0]))
+        work = torch.empty(nbytes, dtype=torch.uint8, device=dev) if nbytes else None
+        _check(_lib().gmcp_dualmesh_embed_ws(_ptr(P), self.N, _ptr(V), _ptr(self.F), self.F.shape[0], _ptr(self.tri),
+                                             _ptr(bary), _ptr(delta), _ptr(self.dist2), _ptr(work), nbytes,
+                                             _stream(dev)), "gmcp_dualmesh_embed")
         self.bary64, self.delta64 = bary, delta
         self.bary = bary.to(dtype).contiguous()
         self.delta = delta.to(dtype).contiguous()
