@@ -34,6 +34,8 @@ namespace {
 using gmcp::kWave;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // four floats of a caller's array, at any float
 
 constexpr int IN = 16, HID = 128, OUT = 16;
 constexpr int64_t OFF_W1 = 0, OFF_B1 = OFF_W1 + IN * HID, OFF_W2 = OFF_B1 + HID, OFF_B2 = OFF_W2 + HID * HID,
@@ -41,43 +43,46 @@ constexpr int64_t OFF_W1 = 0, OFF_B1 = OFF_W1 + IN * HID, OFF_W2 = OFF_B1 + HID,
                   OFF_B4 = OFF_W4 + HID * OUT, N_PARAMS = OFF_B4 + OUT;
 constexpr int ACT = 6 * HID;  // saved activations per row
 
-enum { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_SILU = 2, EPI_SILU_BWD = 3 };
-
-__device__ inline float silu(float z) { return z / (1.0f + __expf(-z)); }
+// 1 + exp(-z), at most 2^126: beyond (z < -87) silu and its derivative are
+// below 1e-35 either way, and the reciprocal stays a normal number
+__device__ inline float one_exp(float z) {
+  return 1.0f + __builtin_amdgcn_exp2f(fminf(z * -1.44269504f, 126.0f));
+}
+// z / d and 1 / d for such a d >= 1 from the hardware reciprocal and one
+// correction step (errors within an ulp, as measured against the division:
+// the IEEE sequence scales for exponents that d cannot have and took most of
+// the activation's instructions)
+__device__ inline float div_one(float z, float d) {
+  const float r = __builtin_amdgcn_rcpf(d), q = z * r;
+  return __builtin_fmaf(__builtin_fmaf(-d, q, z), r, q);
+}
+__device__ inline float silu(float z) { return div_one(z, one_exp(z)); }
 __device__ inline float silu_grad(float z) {
-  float s = 1.0f / (1.0f + __expf(-z));
+  const float s = div_one(1.0f, one_exp(z));
   return s * (1.0f + z * (1.0f - s));
 }
 
-// C = op(A) op(B) (+ bias, SiLU), op(A) is M x K, op(B) is K x N.
+// C = op(A) op(B), op(A) is M x K, op(B) is K x N (gmcp_gemm_bf16).
 // A(m,k) = transA ? A[k*lda + m] : A[m*lda + k]; B(k,n) likewise.
 // Block tile 64 x 64 (four waves of 32 x 32), K step 32 (two MFMAs).
-// Split-K (EPI_STORE): block z handles k in [z*kc, (z+1)*kc) and writes
-// its partial product at C + z * split_stride.  EPI_SILU_BWD multiplies the
-// product by silu'(Z) (Z [M][ldz], the layer's pre-activations): the
-// backward pass's dZ = (dH W^T) * silu'(Z) in the GEMM's epilogue.
-template <int EPI>
 __global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, int lda, int transA,
                                                const float *__restrict__ B, int ldb, int transB, int M, int N, int K,
-                                               int kc, const float *__restrict__ bias, float *__restrict__ C,
-                                               int ldc, float *__restrict__ C2, int64_t split_stride,
-                                               const float *__restrict__ Z, int ldz) {
+                                               float *__restrict__ C, int ldc) {
   __shared__ __bf16 As[64][32 + 8];
   __shared__ __bf16 Bs[32][64 + 8];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w >> 1, wn = w & 1;
   const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int kb = blockIdx.z * kc, ke = min(K, kb + kc);
   f32x16 acc = {};
-  for (int k0 = kb; k0 < ke; k0 += 32) {
+  for (int k0 = 0; k0 < K; k0 += 32) {
     for (int e = tid; e < 64 * 32; e += 256) {
       int r = e >> 5, kk = e & 31, m = m0 + r, k = k0 + kk;
-      float v = (m < M && k < ke) ? (transA ? A[(int64_t)k * lda + m] : A[(int64_t)m * lda + k]) : 0.0f;
+      float v = (m < M && k < K) ? (transA ? A[(int64_t)k * lda + m] : A[(int64_t)m * lda + k]) : 0.0f;
       As[r][kk] = (__bf16)v;
     }
     for (int e = tid; e < 32 * 64; e += 256) {
       int kk = e >> 6, cc = e & 63, k = k0 + kk, n = n0 + cc;
-      float v = (k < ke && n < N) ? (transB ? B[(int64_t)n * ldb + k] : B[(int64_t)k * ldb + n]) : 0.0f;
+      float v = (k < K && n < N) ? (transB ? B[(int64_t)n * ldb + k] : B[(int64_t)k * ldb + n]) : 0.0f;
       Bs[kk][cc] = (__bf16)v;
     }
     __syncthreads();
@@ -99,18 +104,7 @@ __global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, int l
   for (int r = 0; r < 16; ++r) {
     const int m = m0 + wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
     if (m >= M || n >= N) continue;
-    float v = acc[r];
-    if (EPI == EPI_STORE) {
-      C[blockIdx.z * split_stride + (int64_t)m * ldc + n] = v;
-    } else if (EPI == EPI_BIAS) {
-      C[(int64_t)m * ldc + n] = v + bias[n];
-    } else if (EPI == EPI_SILU_BWD) {
-      C[(int64_t)m * ldc + n] = v * silu_grad(Z[(int64_t)m * ldz + n]);
-    } else {
-      float z = v + bias[n];
-      C[(int64_t)m * ldc + n] = z;
-      C2[(int64_t)m * ldc + n] = silu(z);
-    }
+    C[(int64_t)m * ldc + n] = acc[r];
   }
 }
 
@@ -134,24 +128,6 @@ __global__ __launch_bounds__(kWave *kRedGroups) void k_reduce_split(const float 
     for (int k = 0; k < kRedGroups; ++k) t += red[k][e];
     out[i] = t;
   }
-}
-
-// column sums of X [B][ld] (the first ncol <= 128 columns) over chunks of
-// rows_per rows, one chunk per block of 256 threads: thread (h, c) adds
-// column c over the chunk's rows h, h + 2, ... in order, and the two halves
-// are added in LDS (fixed order); part [chunks][ncol]
-constexpr int kColRows = 64;  // rows per chunk
-__global__ __launch_bounds__(2 * HID) void k_colsum_partial(const float *__restrict__ X, int64_t B, int ld, int ncol,
-                                                             int rows_per, float *__restrict__ part) {
-  __shared__ float half[HID];
-  const int c = threadIdx.x & (HID - 1), h = threadIdx.x / HID;
-  const int64_t r0 = (int64_t)blockIdx.x * rows_per, r1 = min(B, r0 + rows_per);
-  float s = 0.0f;
-  if (c < ncol)
-    for (int64_t r = r0 + h; r < r1; r += 2) s += X[r * ld + c];
-  if (h == 1) half[c] = s;
-  __syncthreads();
-  if (h == 0 && c < ncol) part[(int64_t)blockIdx.x * ncol + c] = s + half[c];
 }
 
 // dY = 2 (Y - T) / (B n_out) on the first n_out columns, 0 on the padding;
@@ -217,57 +193,73 @@ __global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float
 constexpr int kFrag = kWave * 8;                     // bf16 per A fragment
 constexpr int kFragL1 = 4, kFragL2 = 32, kFragL3 = 32, kFragL4 = 8;  // 32-feature tiles x k-steps
 constexpr int kFragAll = kFragL1 + kFragL2 + kFragL3 + kFragL4;      // 76 fragments, 76 KB
-constexpr int kFusedWaves = 8;
+// waves per block: one block of 16 fills a compute unit for inference (the
+// weights are staged once per unit); saving the activations needs more
+// registers and is bound by its 3 KB of stores per row
+constexpr int fwd_waves(bool save) { return save ? 8 : 16; }
+constexpr size_t kFwdLds = (size_t)kFragAll * kFrag * sizeof(__bf16) + (3 * HID + OUT) * sizeof(float);
 
-__device__ inline int slot_feature(int s, int h, int j) { return 16 * s + (j >> 2) * 8 + 4 * h + (j & 3); }
-
+// The activations bound it: 384 SiLU per row, each two transcendental
+// instructions (16 cycles a wave) and about eight plain ones; the matrix
+// products of a tile take a quarter of that and overlap other waves'
+// activations.  The tiles of a layer are unrolled, so the next layer's
+// operands are named registers.  262144 rows: 46 us, 420 TFLOP/s (103 us with
+// the IEEE division, rolled tiles whose operands were placed by selects, and
+// two blocks per unit staging the weights).  65536 rows with the activations
+// saved: 60 us, 3.4 TB/s of stores (88 us).
 template <bool SAVE>
-__global__ __launch_bounds__(kWave *kFusedWaves) void k_mlp_fwd(const float *__restrict__ P,
-                                                                const float *__restrict__ x, int64_t B,
-                                                                float *__restrict__ y, float *__restrict__ act) {
+__global__ __launch_bounds__(kWave *fwd_waves(SAVE)) __attribute__((amdgpu_waves_per_eu(SAVE ? 2 : 4))) void k_mlp_fwd(
+    const float *__restrict__ P, const float *__restrict__ x, int64_t B, float *__restrict__ y,
+    float *__restrict__ act) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __bf16 *wf = reinterpret_cast<__bf16 *>(smem);  // [kFragAll][64 lanes][8]
+  bf16x8 *frag = reinterpret_cast<bf16x8 *>(smem);  // [kFragAll][64 lanes]
+  float *sb = reinterpret_cast<float *>(smem + (size_t)kFragAll * kFrag * sizeof(__bf16));  // b1 | b2 | b3 | b4
+  constexpr int kThreadsF = kWave * fwd_waves(SAVE);
+  for (int i = threadIdx.x; i < 3 * HID + OUT; i += kThreadsF)
+    sb[i] = P[i < HID ? OFF_B1 + i : (i < 2 * HID ? OFF_B2 + i - HID : (i < 3 * HID ? OFF_B3 + i - 2 * HID
+                                                                                 : OFF_B4 + i - 3 * HID))];
   // stage: fragment f of layer L = (tile t, k-step s), lane l, slot j holds
-  // W_L[k = slot_feature(s, l >> 5, j)][n = 32 t + (l & 31)] (0 beyond N).
-  // A fragment is the 16 x 32 block of W_L at rows 16 s.., columns 32 t..;
-  // consecutive threads read consecutive columns of a row (coalesced) and
-  // place each value at its lane and slot
-  // (eight loads in flight per thread: the staging is latency-bound)
-  constexpr int kStage = kFragAll * kFrag, kBatch = 8;
-  for (int e0 = threadIdx.x; e0 < kStage; e0 += kBatch * blockDim.x) {
-    float v[kBatch];
-    int dst[kBatch];
+  // W_L[k = 16 s + (j >> 2) * 8 + 4 (l >> 5) + (j & 3)][n = 32 t + (l & 31)]
+  // (0 beyond N): eight loads per lane, each of two runs of 32 columns, and
+  // one 16-byte write.  kBatch fragments are in flight per wave (one pass of
+  // this latency chain is what a small batch takes).
+  constexpr int kLanes = kFragAll * kWave, kBatch = 5;
+  for (int e0 = threadIdx.x; e0 < kLanes; e0 += kBatch * kThreadsF) {
+    float v[kBatch][8];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const int e = e0 + u * blockDim.x;
-      v[u] = 0.0f;
-      dst[u] = -1;
-      if (e < kStage) {
-        const int f = e / kFrag, kl = (e % kFrag) / 32, nl = e % 32;
-        int ff, S, N, K;
-        int64_t off;
-        if (f < kFragL1) { ff = f; S = 1; N = HID; K = IN; off = OFF_W1; }
-        else if (f < kFragL1 + kFragL2) { ff = f - kFragL1; S = 8; N = HID; K = HID; off = OFF_W2; }
-        else if (f < kFragL1 + kFragL2 + kFragL3) { ff = f - kFragL1 - kFragL2; S = 8; N = HID; K = HID; off = OFF_W3; }
-        else { ff = f - kFragL1 - kFragL2 - kFragL3; S = 8; N = OUT; K = HID; off = OFF_W4; }
-        const int t = ff / S, sk = ff % S;
-        const int n = 32 * t + nl, k = 16 * sk + kl;
-        // k local = (j >> 2) * 8 + 4 h + (j & 3)  <=>  h = (kl >> 2) & 1, j = (kl >> 3) * 4 + (kl & 3)
-        const int h = (kl >> 2) & 1, j = ((kl >> 3) << 2) | (kl & 3);
-        dst[u] = f * kFrag + (nl + 32 * h) * 8 + j;
-        if (n < N && k < K) v[u] = P[off + (int64_t)k * N + n];
-      }
+      const int f = (e0 + u * kThreadsF) / kWave, l = threadIdx.x % kWave;
+      int ff, S, N;
+      int64_t off;
+      if (f < kFragL1) { ff = f; S = 1; N = HID; off = OFF_W1; }
+      else if (f < kFragL1 + kFragL2) { ff = f - kFragL1; S = 8; N = HID; off = OFF_W2; }
+      else if (f < kFragL1 + kFragL2 + kFragL3) { ff = f - kFragL1 - kFragL2; S = 8; N = HID; off = OFF_W3; }
+      else { ff = f - kFragL1 - kFragL2 - kFragL3; S = 8; N = OUT; off = OFF_W4; }
+      const int n = 32 * (ff / S) + (l & 31), k0 = 16 * (ff % S) + 4 * (l >> 5);
+      const bool on = f < kFragAll && n < N;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[u][j] = on ? P[off + (int64_t)(k0 + (j >> 2) * 8 + (j & 3)) * N + n] : 0.0f;
     }
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u)
-      if (dst[u] >= 0) wf[dst[u]] = (__bf16)v[u];
+    for (int u = 0; u < kBatch; ++u) {
+      const int e = e0 + u * kThreadsF;
+      bf16x8 o;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) o[j] = (__bf16)v[u][j];
+      if (e < kLanes) frag[e] = o;
+    }
   }
   __syncthreads();
   const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
   const int h = lane >> 5;
   const int64_t tiles = (B + 31) / 32;
-  const bf16x8 *frag = reinterpret_cast<const bf16x8 *>(wf);  // frag[f * 64 + lane]
-  for (int64_t tile = (int64_t)blockIdx.x * kFusedWaves + w; tile < tiles; tile += (int64_t)gridDim.x * kFusedWaves) {
+  // neighbouring tiles go to different blocks: a batch of few tiles spreads
+  // over the compute units
+  for (int64_t tile = (int64_t)w * gridDim.x + blockIdx.x; tile < tiles;
+       tile += (int64_t)gridDim.x * fwd_waves(SAVE)) {
+    // the weights are read from LDS for every tile: kept in registers across
+    // tiles (they do not change) they would spill
+    asm volatile("" ::: "memory");
     const int64_t row = tile * 32 + (lane & 31);
     const bool live = row < B;
     // layer 1 input: x features {4h..4h+3, 8+4h..8+4h+3} of the lane's row
@@ -281,21 +273,18 @@ __global__ __launch_bounds__(kWave *kFusedWaves) void k_mlp_fwd(const float *__r
       bin[0] = (__bf16)a.x; bin[1] = (__bf16)a.y; bin[2] = (__bf16)a.z; bin[3] = (__bf16)a.w;
       bin[4] = (__bf16)c.x; bin[5] = (__bf16)c.y; bin[6] = (__bf16)c.z; bin[7] = (__bf16)c.w;
     }
-    // a layer's output as the next layer's B operands (one per k-step);
-    // tiles run one at a time (not unrolled, so few fragments are in flight)
-    // and their operands are placed by selects, keeping every index static
-    bf16x8 hcur[8], hnext[8];
     // bias + SiLU on the accumulator of output tile t, optional save of Z and
-    // H, and the bf16 operands of k-steps 2t (lo) and 2t + 1 (hi)
-    auto epilogue = [&](const f32x16 &acc, int t, const float *bias, int save_off) {
-      bf16x8 lo, hi;
+    // H; the 16 values are the bf16 operands of k-steps 2t (lo) and 2t + 1
+    // (hi) of the next layer
+    auto epilogue = [&](const f32x16 &acc, int t, const float *bias, int save_off, bf16x8 &lo, bf16x8 &hi) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {  // four groups of four consecutive features
         const int f0 = 32 * t + q * 8 + 4 * h;
-        float z[4], hv[4];
+        const float4 bv = *reinterpret_cast<const float4 *>(bias + f0);
+        const float z[4] = {acc[4 * q] + bv.x, acc[4 * q + 1] + bv.y, acc[4 * q + 2] + bv.z, acc[4 * q + 3] + bv.w};
+        float hv[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          z[i] = acc[4 * q + i] + bias[f0 + i];
           hv[i] = silu(z[i]);
           if (q < 2) lo[4 * q + i] = (__bf16)hv[i];
           else hi[4 * (q - 2) + i] = (__bf16)hv[i];
@@ -306,49 +295,40 @@ __global__ __launch_bounds__(kWave *kFusedWaves) void k_mlp_fwd(const float *__r
               make_float4(hv[0], hv[1], hv[2], hv[3]);
         }
       }
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        if (k == 2 * t) hnext[k] = lo;
-        if (k == 2 * t + 1) hnext[k] = hi;
-      }
     };
+    bf16x8 h1[8], h2[8];
     // layer 1: K = 16, one k-step
-#pragma unroll 1
+#pragma unroll
     for (int t = 0; t < 4; ++t) {
       f32x16 zero = {};
       const f32x16 a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[t * kWave + lane], bin, zero, 0, 0, 0);
-      epilogue(a, t, P + OFF_B1, 0);
+      epilogue(a, t, sb, 0, h1[2 * t], h1[2 * t + 1]);
     }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) hcur[k] = hnext[k];
     // layers 2 and 3: K = 128, eight k-steps per output tile
-#pragma unroll 1
-    for (int L = 0; L < 2; ++L) {
-      const int fbase = kFragL1 + L * kFragL2;
-#pragma unroll 1
+    auto layer = [&](int fbase, const bf16x8 *in, bf16x8 *out, const float *bias, int save_off) {
+#pragma unroll
       for (int t = 0; t < 4; ++t) {
         f32x16 a = {};
 #pragma unroll
         for (int sk = 0; sk < 8; ++sk)
-          a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[(fbase + t * 8 + sk) * kWave + lane], hcur[sk], a, 0, 0,
-                                                      0);
-        epilogue(a, t, P + (L == 0 ? OFF_B2 : OFF_B3), (L + 1) * 2 * HID);
+          a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[(fbase + t * 8 + sk) * kWave + lane], in[sk], a, 0, 0, 0);
+        epilogue(a, t, bias, save_off, out[2 * t], out[2 * t + 1]);
       }
-#pragma unroll
-      for (int k = 0; k < 8; ++k) hcur[k] = hnext[k];
-    }
+    };
+    layer(kFragL1, h1, h2, sb + HID, 2 * HID);
+    layer(kFragL1 + kFragL2, h2, h1, sb + 2 * HID, 4 * HID);
     // layer 4: one 32-feature tile, the first 16 are the outputs
     {
       const int fbase = kFragL1 + kFragL2 + kFragL3;
       f32x16 a = {};
 #pragma unroll
       for (int sk = 0; sk < 8; ++sk)
-        a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[(fbase + sk) * kWave + lane], hcur[sk], a, 0, 0, 0);
+        a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[(fbase + sk) * kWave + lane], h1[sk], a, 0, 0, 0);
       if (live) {
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
           const int f0 = q * 8 + 4 * h;
-          const float *b4 = P + OFF_B4;
+          const float *b4 = sb + 3 * HID;
           *reinterpret_cast<float4 *>(y + row * OUT + f0) =
               make_float4(a[4 * q] + b4[f0], a[4 * q + 1] + b4[f0 + 1], a[4 * q + 2] + b4[f0 + 2],
                           a[4 * q + 3] + b4[f0 + 3]);
@@ -358,19 +338,235 @@ __global__ __launch_bounds__(kWave *kFusedWaves) void k_mlp_fwd(const float *__r
   }
 }
 
-inline unsigned nb(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
+// --------------------------------------------------------------- fused backward
+// Gradients of all parameters in one pass over the batch, 256 rows per block
+// at a time.  Each of the 16 waves takes 16 rows through the chain
+//   dZ3 = (dY W4^T) silu'(Z3),  dZ2 = (dZ3 W3^T) silu'(Z2),  dZ1 likewise,
+// transposed as in the forward pass (features x rows, here on
+// v_mfma_f32_16x16x32_bf16: lane l holds row l & 15 and features 4 (l >> 4) ..
+// + 3 of a 16-feature tile), so that a layer's dZ is the next product's
+// operand in registers when the k slots follow that order (W staged once per
+// block as bf16 A fragments).  A layer's dZ also goes to LDS in bf16,
+// feature-major (two rows per word, neighbouring lanes exchange), where the
+// block's waves read it as the operand of dW = H^T dZ: each wave owns one
+// 32 x 32 tile of the gradient and reads H's columns from memory with
+// coalesced loads.  The gradients stay in accumulators over all of the
+// block's rows; one partial per block is written and k_reduce_split adds
+// them in block order.  Bias gradients are sums of the float dZ over the
+// lanes (rows of 16 with DPP), then over the waves in order.
+//
+// Bound by latency: 201 MB of activations (41 us at the copy rate) and about
+// 25 us of SiLU derivatives and products pass through phases that the block
+// takes together.  65536 rows: 75 us and 13 us for the partials' sum;
+// one GEMM per product with 64 x 64 tiles staged through scalar LDS writes,
+// float dZ in memory between them, split partials for each weight and
+// column-sum launches took 560 us.  Eight waves of 32 rows (250 registers)
+// took 220 us and loads behind per-lane conditions 240 us; the activations
+// are loaded four tiles at a time because eight spill.
+constexpr int kBwdWaves = 16;
+constexpr int kBwdRows = 16 * kBwdWaves;
+constexpr int kBwdBlocks = 256;                       // partials at most: a block per compute unit
+constexpr int kBwdL4 = 8, kBwdL = 32;                 // fragments: W4 8 tiles x 1 k-step, W3 and W2 8 x 4
+constexpr int kBwdFrags = kBwdL4 + 2 * kBwdL;
+constexpr int kTPitch = kBwdRows + 8;                 // bf16 per feature (a pitch of 4 words modulo the banks)
+constexpr size_t kBwdW = (size_t)kBwdFrags * kFrag * sizeof(__bf16), kBwdT = (size_t)HID * kTPitch * sizeof(__bf16);
+constexpr size_t kBwdLds = kBwdW + kBwdT + sizeof(float) * kBwdWaves * (HID + OUT);
 
-template <int EPI>
-hipError_t gemm(hipStream_t s, const float *A, int lda, int tA, const float *B, int ldb, int tB, int M, int N, int K,
-                const float *bias, float *C, int ldc, float *C2, int splits = 1, int64_t split_stride = 0,
-                const float *Z = nullptr, int ldz = 0) {
-  int kc = (K + splits - 1) / splits;
-  kc = (kc + 31) / 32 * 32;
-  dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)splits);
-  hipLaunchKernelGGL(k_gemm<EPI>, grid, dim3(256), 0, s, A, lda, tA, B, ldb, tB, M, N, K, kc, bias, C, ldc, C2,
-                     split_stride, Z, ldz);
-  return hipGetLastError();
+// v plus the lane CTRL names (within rows of 16)
+template <int CTRL>
+__device__ inline float add_lane(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf,
+                                                                   false));
 }
+// sum over the lane's row of 16, in every lane
+__device__ inline float row16_sum(float v) {
+  v = add_lane<0xB1>(v);   // 1 lane apart
+  v = add_lane<0x4E>(v);   // 2
+  v = add_lane<0x141>(v);  // mirror of 8
+  return add_lane<0x140>(v);  // mirror of 16
+}
+
+__global__ __launch_bounds__(kWave *kBwdWaves) void k_mlp_bwd(const float *__restrict__ P,
+                                                              const float *__restrict__ x,
+                                                              const float *__restrict__ act,
+                                                              const float *__restrict__ dy, int64_t B,
+                                                              float *__restrict__ part) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  bf16x8 *frag = reinterpret_cast<bf16x8 *>(smem);                 // [kBwdFrags][64]
+  __bf16 *T = reinterpret_cast<__bf16 *>(smem + kBwdW);            // [128 features][kTPitch rows]
+  float *red = reinterpret_cast<float *>(smem + kBwdW + kBwdT);    // [waves][128], bias sums of a layer
+  float *red4 = red + kBwdWaves * HID;                             // [waves][16], of the output layer
+  const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+  const int g16 = lane >> 4, r16 = lane & 15, h = lane >> 5, r32 = lane & 31;
+  // stage: fragment (layer, tile t, k-step s), lane l, slot j holds
+  // W[16 t + (l & 15)][32 s + 16 (j >> 2) + 4 (l >> 4) + (j & 3)]
+  for (int e = threadIdx.x; e < kBwdFrags * kWave; e += kWave * kBwdWaves) {
+    const int f = e / kWave;
+    const int S = f < kBwdL4 ? 1 : 4, N = f < kBwdL4 ? OUT : HID, ff = f < kBwdL4 ? f : (f - kBwdL4) % kBwdL;
+    const float *src = P + (f < kBwdL4 ? OFF_W4 : (f < kBwdL4 + kBwdL ? OFF_W3 : OFF_W2)) +
+                       (16 * (ff / S) + r16) * N + 32 * (ff % S) + 4 * g16;
+    f32x4 a = *reinterpret_cast<const f32x4u *>(src), c = {};
+    if (N == HID) c = *reinterpret_cast<const f32x4u *>(src + 16);
+    bf16x8 v;
+    v[0] = (__bf16)a.x; v[1] = (__bf16)a.y; v[2] = (__bf16)a.z; v[3] = (__bf16)a.w;
+    v[4] = (__bf16)c.x; v[5] = (__bf16)c.y; v[6] = (__bf16)c.z; v[7] = (__bf16)c.w;
+    frag[e] = v;
+  }
+  const int ft = w >> 2, nt = w & 3;        // the wave's tile of dW3 and dW2: inputs 32 ft.., outputs 32 nt..
+  f32x16 g3 = {}, g2 = {};
+  const int xt = w & 7, xk = w >> 3;        // and of dW4 and dW1: 16 inputs / outputs 16 xt.., half xk of the rows
+  f32x4 g4 = {}, g1 = {};
+  float b1 = 0.0f, b2 = 0.0f, b3 = 0.0f, b4 = 0.0f;  // bias gradients of feature threadIdx.x
+  __syncthreads();
+  for (int64_t row0 = (int64_t)blockIdx.x * kBwdRows; row0 < B; row0 += (int64_t)gridDim.x * kBwdRows) {
+    // Rows beyond the batch read the last row: their dY is set to 0, so their
+    // dZ and their share of every sum are 0.  (Loads behind a per-lane
+    // condition were waited for one by one.)
+    const int64_t row = row0 + 16 * w + r16, rowc = row < B ? row : B - 1;
+    const int last = (int)(B - 1 - row0 < kBwdRows - 1 ? B - 1 - row0 : kBwdRows - 1);
+    // rows r .. r + 7 of a column of X [B][ld] as an MFMA operand
+    auto rows8 = [&](const float *X, int ld, int r) {
+      const float *p = X + row0 * ld;
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = p[min(r + j, last) * ld];
+      bf16x8 o;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) o[j] = (__bf16)v[j];
+      return o;
+    };
+    auto dy_op = [&](int r) {  // rows8 of dY, 0 beyond the batch
+      bf16x8 o = rows8(dy + r16, OUT, r);
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (r + j > last) o[j] = (__bf16)0.0f;
+      return o;
+    };
+    f32x4 z[4];
+    auto load_z = [&](int z_off) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        z[t] = *reinterpret_cast<const f32x4u *>(act + rowc * ACT + z_off + 16 * t + 4 * g16);
+    };
+    // dZ^T of a layer: the products of S k-steps times silu'(Z), to `out`
+    // (operands of the next layer), T and red
+    auto chain = [&](int fbase, int S, const bf16x8 *in, bf16x8 *out, int z_off) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        if (t == 0) load_z(z_off);
+        if (t == 4) load_z(z_off + 64);
+        f32x4 a = {};
+#pragma unroll
+        for (int sk = 0; sk < S; ++sk)
+          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag[(fbase + t * S + sk) * kWave + lane], in[sk], a, 0, 0, 0);
+        float sum[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float v = a[i] * silu_grad(z[t & 3][i]);
+          out[t >> 1][4 * (t & 1) + i] = (__bf16)v;
+          sum[i] = row16_sum(v);
+        }
+        if (r16 == 0)
+          *reinterpret_cast<float4 *>(red + w * HID + 16 * t + 4 * g16) = make_float4(sum[0], sum[1], sum[2], sum[3]);
+        // features f, f + 1 of rows r, r + 1: the even lane writes f, the odd one f + 1
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const uint32_t mine = __builtin_bit_cast(uint4, out[t >> 1])[2 * (t & 1) + k];
+          const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xf, 0xf, false);
+          const uint32_t two = (lane & 1) ? (other >> 16) | (mine & 0xffff0000u) : (mine & 0xffffu) | (other << 16);
+          *reinterpret_cast<uint32_t *>(T + (16 * t + 4 * g16 + 2 * k + (lane & 1)) * kTPitch + 16 * w + (r16 & ~1)) = two;
+        }
+      }
+    };
+    auto wgrad = [&](int h_off, f32x16 &g) {
+      const float *X = act + h_off + 32 * ft + r32;
+      const __bf16 *D = T + (32 * nt + r32) * kTPitch + 8 * h;
+#pragma unroll 4
+      for (int ks = 0; ks < kBwdRows / 16; ++ks)
+        g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows8(X, ACT, 16 * ks + 8 * h),
+                                                    *reinterpret_cast<const bf16x8 *>(D + 16 * ks), g, 0, 0, 0);
+    };
+    auto bias = [&](float &b) {  // waves in order
+      if (threadIdx.x < HID)
+        for (int k = 0; k < kBwdWaves; ++k) b += red[k * HID + threadIdx.x];
+    };
+    // output layer: dY as the first operand (the k-step's second half is zero), db4
+    bf16x8 d0[4], d1[4];
+    {
+      f32x4 v = *reinterpret_cast<const f32x4u *>(dy + rowc * OUT + 4 * g16);
+      if (row >= B) v = f32x4{};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        d0[0][j] = (__bf16)v[j];
+        d0[0][4 + j] = (__bf16)0.0f;
+        const float sum = row16_sum(v[j]);
+        if (r16 == 0) red4[w * OUT + 4 * g16 + j] = sum;
+      }
+    }
+    chain(0, 1, d0, d1, 4 * HID);
+    __syncthreads();
+    if (threadIdx.x < OUT)
+      for (int k = 0; k < kBwdWaves; ++k) b4 += red4[k * OUT + threadIdx.x];
+    bias(b3);
+    // dW4 = H3^T dY: 16 x 16 tiles, half of the rows per wave
+#pragma unroll 2
+    for (int ks = 0; ks < kBwdRows / 64; ++ks) {
+      const int r = (kBwdRows / 2) * xk + 32 * ks + 8 * g16;
+      g4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rows8(act + 5 * HID + 16 * xt + r16, ACT, r),
+                                                   dy_op(r), g4, 0, 0, 0);
+    }
+    wgrad(3 * HID, g3);
+    __syncthreads();
+    chain(kBwdL4, 4, d1, d0, 2 * HID);
+    __syncthreads();
+    bias(b2);
+    wgrad(HID, g2);
+    __syncthreads();
+    chain(kBwdL4 + kBwdL, 4, d0, d1, 0);
+    __syncthreads();
+    bias(b1);
+    // dW1 = x^T dZ1
+#pragma unroll 2
+    for (int ks = 0; ks < kBwdRows / 64; ++ks) {
+      const int r = (kBwdRows / 2) * xk + 32 * ks + 8 * g16;
+      g1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          rows8(x + r16, IN, r), *reinterpret_cast<const bf16x8 *>(T + (16 * xt + r16) * kTPitch + r), g1, 0, 0, 0);
+    }
+    __syncthreads();
+  }
+  // the block's partial gradient; register r of a 32 x 32 tile is row
+  // (r >> 2) * 8 + 4 h + (r & 3), of a 16 x 16 tile row 4 (l >> 4) + r
+  float *out = part + (int64_t)blockIdx.x * N_PARAMS;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int at = (32 * ft + (r >> 2) * 8 + 4 * h + (r & 3)) * HID + 32 * nt + r32;
+    out[OFF_W3 + at] = g3[r];
+    out[OFF_W2 + at] = g2[r];
+  }
+  // dW4 and dW1: the second half of the rows through LDS, added to the first
+  float *half = reinterpret_cast<float *>(T);
+  static_assert(kBwdT >= sizeof(float) * 8 * kWave * 8, "the second halves fit");
+  if (xk == 1)
+    for (int r = 0; r < 4; ++r) {
+      half[(r * 8 + xt) * kWave + lane] = g4[r];
+      half[((4 + r) * 8 + xt) * kWave + lane] = g1[r];
+    }
+  __syncthreads();
+  if (xk == 0)
+    for (int r = 0; r < 4; ++r) {
+      const int m = 4 * g16 + r;
+      out[OFF_W4 + (16 * xt + m) * OUT + r16] = g4[r] + half[(r * 8 + xt) * kWave + lane];
+      out[OFF_W1 + m * HID + 16 * xt + r16] = g1[r] + half[((4 + r) * 8 + xt) * kWave + lane];
+    }
+  if (threadIdx.x < HID) {
+    out[OFF_B1 + threadIdx.x] = b1;
+    out[OFF_B2 + threadIdx.x] = b2;
+    out[OFF_B3 + threadIdx.x] = b3;
+  }
+  if (threadIdx.x < OUT) out[OFF_B4 + threadIdx.x] = b4;
+}
+
+inline unsigned nb(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
 // Device address of `scratch` on the current device, looked up once per
 // device (with that device current) and kept.
@@ -397,9 +593,8 @@ int scratch_address(hipStream_t s, float **out) {
   return GMCP_OK;
 }
 
-constexpr int kSplitRows = 512;  // batch rows per split-K chunk of a weight gradient (enough blocks to fill the device)
-
-int splits_for(int64_t B) { return (int)std::max<int64_t>(1, std::min<int64_t>(256, (B + kSplitRows - 1) / kSplitRows)); }
+// blocks of the backward pass, one partial gradient each
+unsigned bwd_blocks(int64_t B) { return (unsigned)std::min<int64_t>(kBwdBlocks, (B + kBwdRows - 1) / kBwdRows); }
 
 }  // namespace
 
@@ -407,21 +602,13 @@ extern "C" {
 
 int64_t gmcp_mlp_param_count(void) { return N_PARAMS; }
 
-size_t gmcp_mlp_work_bytes(int64_t B) {
-  int S = splits_for(B);
-  // two [B][128] gradient buffers, split partials for the largest weight,
-  // column-sum partials, loss partials
-  return sizeof(float) * ((size_t)2 * B * HID + (size_t)S * HID * HID + (size_t)((B + kColRows - 1) / kColRows + 1) * HID +
-                          (size_t)(B * OUT + 255) / 256 + 64);
-}
+size_t gmcp_mlp_work_bytes(int64_t B) { return B > 0 ? sizeof(float) * (size_t)bwd_blocks(B) * N_PARAMS : 0; }
 
 int gmcp_mlp_forward(const float *params, const float *x, int64_t B, float *y, float *act, void *stream) {
   if (!params || !x || !y || B <= 0 || B > (int64_t(1) << 30)) return GMCP_E_ARG;
   hipStream_t s = (hipStream_t)stream;
   // one fused launch: every wave runs the whole network on 32 rows at a
-  // time (weights staged once per block); two blocks fit a CU's LDS
-  // persistent grid: two blocks per compute unit (their LDS), each walking
-  // many row tiles, so the weights are staged once per block
+  // time; a block per compute unit at most, which stages the weights once
   static int n_cu[kMaxDevices] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return GMCP_E_HIP;
@@ -429,13 +616,12 @@ int gmcp_mlp_forward(const float *params, const float *x, int64_t B, float *y, f
                              hipSuccess || n_cu[dev] < 1))
     n_cu[dev] = 256;
   const int64_t tiles = (B + 31) / 32;
-  const int64_t want = (tiles + kFusedWaves - 1) / kFusedWaves;
-  const unsigned grid = (unsigned)std::min<int64_t>(want, 2 * (int64_t)n_cu[dev]);
-  const size_t lds = (size_t)kFragAll * kFrag * sizeof(__bf16);
+  const unsigned grid = (unsigned)std::min<int64_t>(tiles, n_cu[dev]);
+  const size_t lds = kFwdLds;
   if (act)
-    hipLaunchKernelGGL(k_mlp_fwd<true>, dim3(grid), dim3(kWave * kFusedWaves), lds, s, params, x, B, y, act);
+    hipLaunchKernelGGL(k_mlp_fwd<true>, dim3(grid), dim3(kWave * fwd_waves(true)), lds, s, params, x, B, y, act);
   else
-    hipLaunchKernelGGL(k_mlp_fwd<false>, dim3(grid), dim3(kWave * kFusedWaves), lds, s, params, x, B, y, act);
+    hipLaunchKernelGGL(k_mlp_fwd<false>, dim3(grid), dim3(kWave * fwd_waves(false)), lds, s, params, x, B, y, act);
   return hipGetLastError() == hipSuccess ? GMCP_OK : GMCP_E_HIP;
 }
 
@@ -444,59 +630,12 @@ int gmcp_mlp_backward(const float *params, const float *x, const float *act, con
   if (!params || !x || !act || !dy || !grad || !work || B <= 0 || B > (int64_t(1) << 30)) return GMCP_E_ARG;
   if (work_bytes < gmcp_mlp_work_bytes(B)) return GMCP_E_ARG;
   hipStream_t s = (hipStream_t)stream;
-  const float *P = params;
-  const int S = splits_for(B);
-  float *dA = (float *)work;                 // [B][128]
-  float *dB = dA + (size_t)B * HID;          // [B][128]
-  float *part = dB + (size_t)B * HID;        // [S][128][128]
-  float *cpart = part + (size_t)S * HID * HID;
-  const int rows_per = kColRows;
-  const unsigned cblocks = (unsigned)((B + rows_per - 1) / rows_per);
-  const float *Z1 = act, *H1 = act + HID, *Z2 = act + 2 * HID, *H2 = act + 3 * HID, *Z3 = act + 4 * HID,
-              *H3 = act + 5 * HID;
-  const int ld = ACT;
-  hipError_t e = hipSuccess;
-  auto wgrad = [&](const float *Hin, int ldh, int fin, const float *dZ, int ldz, int fout, float *dW) {
-    // dW [fin][fout] = Hin^T dZ over the batch, split-K partials then a fixed-order sum
-    if (e == hipSuccess)
-      e = gemm<EPI_STORE>(s, Hin, ldh, 1, dZ, ldz, 0, fin, fout, (int)B, nullptr, part, fout, nullptr, S,
-                          (int64_t)fin * fout);
-    if (e == hipSuccess) {
-      hipLaunchKernelGGL(k_reduce_split, dim3(nb((int64_t)fin * fout, kWave)), dim3(kWave * kRedGroups), 0, s, part,
-                         S, (int64_t)fin * fout, dW);
-      e = hipGetLastError();
-    }
-  };
-  auto bgrad = [&](const float *dZ, int ldz, int ncol, float *db) {
-    if (e != hipSuccess) return;
-    hipLaunchKernelGGL(k_colsum_partial, dim3(cblocks), dim3(2 * HID), 0, s, dZ, B, ldz, ncol, rows_per, cpart);
-    hipLaunchKernelGGL(k_reduce_split, dim3(nb(ncol, kWave)), dim3(kWave * kRedGroups), 0, s, cpart, (int)cblocks,
-                       (int64_t)ncol, db);
-    e = hipGetLastError();
-  };
-  // layer 4: Y = H3 W4 + b4; each dZ of the layers below comes out of the
-  // GEMM with silu'(Z) applied in its epilogue (dA and dB alternate)
-  wgrad(H3, ld, HID, dy, OUT, OUT, grad + OFF_W4);
-  bgrad(dy, OUT, OUT, grad + OFF_B4);
-  if (e == hipSuccess)
-    e = gemm<EPI_SILU_BWD>(s, dy, OUT, 0, P + OFF_W4, OUT, 1, (int)B, HID, OUT, nullptr, dB, HID, nullptr, 1, 0, Z3,
-                           ld);
-  // layer 3
-  wgrad(H2, ld, HID, dB, HID, HID, grad + OFF_W3);
-  bgrad(dB, HID, HID, grad + OFF_B3);
-  if (e == hipSuccess)
-    e = gemm<EPI_SILU_BWD>(s, dB, HID, 0, P + OFF_W3, HID, 1, (int)B, HID, HID, nullptr, dA, HID, nullptr, 1, 0, Z2,
-                           ld);
-  // layer 2
-  wgrad(H1, ld, HID, dA, HID, HID, grad + OFF_W2);
-  bgrad(dA, HID, HID, grad + OFF_B2);
-  if (e == hipSuccess)
-    e = gemm<EPI_SILU_BWD>(s, dA, HID, 0, P + OFF_W2, HID, 1, (int)B, HID, HID, nullptr, dB, HID, nullptr, 1, 0, Z1,
-                           ld);
-  // layer 1
-  wgrad(x, IN, IN, dB, HID, HID, grad + OFF_W1);
-  bgrad(dB, HID, HID, grad + OFF_B1);
-  return e == hipSuccess ? GMCP_OK : GMCP_E_HIP;
+  const unsigned blocks = bwd_blocks(B);
+  float *part = (float *)work;
+  hipLaunchKernelGGL(k_mlp_bwd, dim3(blocks), dim3(kWave * kBwdWaves), kBwdLds, s, params, x, act, dy, B, part);
+  hipLaunchKernelGGL(k_reduce_split, dim3(nb(N_PARAMS, kWave)), dim3(kWave * kRedGroups), 0, s, part, (int)blocks,
+                     N_PARAMS, grad);
+  return hipGetLastError() == hipSuccess ? GMCP_OK : GMCP_E_HIP;
 }
 
 int gmcp_mlp_mse(const float *y, const float *t, int64_t B, int n_out, float *loss, float *dy, void *work,
@@ -539,10 +678,9 @@ int gmcp_mlp_adam(float *params, const float *grad, float *m, float *v, int64_t 
 int gmcp_gemm_bf16(const float *A, int lda, int transA, const float *B, int ldb, int transB, int M, int N, int K,
                    float *C, int ldc, void *stream) {
   if (!A || !B || !C || M <= 0 || N <= 0 || K <= 0) return GMCP_E_ARG;
-  return gemm<EPI_STORE>((hipStream_t)stream, A, lda, transA, B, ldb, transB, M, N, K, nullptr, C, ldc, nullptr) ==
-                 hipSuccess
-             ? GMCP_OK
-             : GMCP_E_HIP;
+  hipLaunchKernelGGL(k_gemm, dim3((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64)), dim3(256), 0,
+                     (hipStream_t)stream, A, lda, transA, B, ldb, transB, M, N, K, C, ldc);
+  return hipGetLastError() == hipSuccess ? GMCP_OK : GMCP_E_HIP;
 }
 
 }  // extern "C"
