@@ -77,70 +77,80 @@ struct NarrowArgs {
   int64_t cap_pairs;
   int32_t *mp_cnt;  // pairs per master triangle (counted where the pairs are written)
   int32_t *atile, *atile_cnt;  // tiles with selected samples (read by the linearised step bound)
-  const uint32_t *tile_act, *epoch;  // nullable: tiles the last broad phase listed (others have no candidates)
+  const int32_t *ntile, *ntile_cnt;  // the tiles the last broad phase listed (the others have no candidates)
   double *tile_E;
   DevStatus *st;
   bool features;                                   // clipped samples: edge and point samples too
   const int32_t *m_opp, *m_vt_off, *m_vt;          // master edge neighbours, vertex adjacency
 };
 
-// Narrow phase: one wave per work tile, kNarrowWaves tiles per block.  The
-// records and pairs of a block are allocated together (wave counts in LDS,
-// one pair of atomics per block), so every wave of a block passes through
-// that allocation exactly once, whatever its tile holds.
+// Entry of a list of n that virtual block v stands for: the list is split
+// into eight runs, one per XCD (blocks go to the XCDs in turn), so that
+// neighbouring entries share an L2 and every XCD gets an eighth of the work;
+// -1 past the XCD's run.
+__device__ inline int xcd_entry(int v, int n) {
+  const int per = (n + 7) >> 3, at = (v & 7) * per + (v >> 3);
+  return (v >> 3) < per && at < n ? at : -1;
+}
+
+// Narrow phase: one wave per listed work tile, narrow_waves tiles per block.
+// The broad phase lists the tiles with a candidate: a launch over all tiles
+// spent its time on the others (256 environments: 1.22 -> 1.14 ms) and the
+// clustered tiles of one contact patch fell on few XCDs (large indentation
+// 45 -> 41.6 us, its clipped samples 281 -> 231 us).  The records and pairs
+// of a block are allocated together (wave counts in LDS, one pair of atomics
+// per block), so every wave of a block passes through that allocation
+// exactly once, whatever its tile holds.
 template <typename R> constexpr int narrow_waves() { return sizeof(R) == 4 ? 8 : 4; }
 
 template <typename R>
-__device__ __forceinline__ void narrow_body(const NarrowArgs<R> &a) {
-  constexpr int kNW = narrow_waves<R>();
+struct NarrowLds {
   // a wave's staged candidates and, once its candidate loop is done, its
   // sample records share one LDS slot per lane (more resident blocks)
-  __shared__ NarrowSlot<R> nl[kNW][kWave];
-  __shared__ unsigned int alloc_r[kNW], alloc_p[kNW], alloc_t[kNW];
-  __shared__ unsigned long long alloc_rb, alloc_pb;
-  __shared__ int alloc_tb;
+  NarrowSlot<R> nl[narrow_waves<R>()][kWave];
+  unsigned int alloc_r[narrow_waves<R>()], alloc_p[narrow_waves<R>()], alloc_t[narrow_waves<R>()];
+  unsigned long long alloc_rb, alloc_pb;
+  int alloc_tb;
+};
+
+// one turn of the block; tile_id -1: nothing for this wave
+template <typename R>
+__device__ __forceinline__ void narrow_tile(const NarrowArgs<R> &a, NarrowLds<R> &lds, const int tile_id) {
+  constexpr int kNW = narrow_waves<R>();
+  auto &nl = lds.nl;
   const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
   // the block's allocation: every wave calls it once (two block barriers);
   // a wave with records also takes a slot of the active-tile list
   int tslot = -1;
   auto allocate = [&](int nrec, int npair, unsigned long long &rb, unsigned long long &pb) {
     if (lane == 0) {
-      alloc_r[w] = (unsigned)nrec;
-      alloc_p[w] = (unsigned)npair;
-      alloc_t[w] = nrec > 0 ? 1u : 0u;
+      lds.alloc_r[w] = (unsigned)nrec;
+      lds.alloc_p[w] = (unsigned)npair;
+      lds.alloc_t[w] = nrec > 0 ? 1u : 0u;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
       unsigned long long tr = 0, tp = 0;
       unsigned tt = 0;
       for (int i = 0; i < kNW; ++i) {
-        const unsigned r0 = alloc_r[i], p0 = alloc_p[i], t0 = alloc_t[i];
-        alloc_r[i] = (unsigned)tr;
-        alloc_p[i] = (unsigned)tp;
-        alloc_t[i] = tt;
+        const unsigned r0 = lds.alloc_r[i], p0 = lds.alloc_p[i], t0 = lds.alloc_t[i];
+        lds.alloc_r[i] = (unsigned)tr;
+        lds.alloc_p[i] = (unsigned)tp;
+        lds.alloc_t[i] = tt;
         tr += r0;
         tp += p0;
         tt += t0;
       }
-      alloc_rb = tr ? atomicAdd(&a.st->n_active, tr) : 0;
-      alloc_pb = tp ? atomicAdd(&a.st->n_pairs, tp) : 0;
-      alloc_tb = (tt && a.atile) ? atomicAdd(a.atile_cnt, (int)tt) : 0;
+      lds.alloc_rb = tr ? atomicAdd(&a.st->n_active, tr) : 0;
+      lds.alloc_pb = tp ? atomicAdd(&a.st->n_pairs, tp) : 0;
+      lds.alloc_tb = tt ? atomicAdd(a.atile_cnt, (int)tt) : 0;
     }
     __syncthreads();
-    rb = alloc_rb + alloc_r[w];
-    pb = alloc_pb + alloc_p[w];
-    if (nrec > 0) tslot = alloc_tb + (int)alloc_t[w];
+    rb = lds.alloc_rb + lds.alloc_r[w];
+    pb = lds.alloc_pb + lds.alloc_p[w];
+    if (nrec > 0) tslot = lds.alloc_tb + (int)lds.alloc_t[w];
   };
-  const int tile_id = xcd_block(blockIdx.x, gridDim.x) * kNW + w;
-  if (tile_id >= a.n_tiles) {
-    unsigned long long rb, pb;
-    allocate(0, 0, rb, pb);
-    return;
-  }
-  // a tile none of whose triangles the broad phase listed has no candidates
-  // (the broad phase emptied their per-triangle outputs): one load decides
-  if (a.tile_act && a.tile_act[tile_id] != *a.epoch) {
-    if (lane == 0) a.tile_E[tile_id] = 0.0;
+  if (tile_id < 0) {
     unsigned long long rb, pb;
     allocate(0, 0, rb, pb);
     return;
@@ -374,7 +384,7 @@ __device__ __forceinline__ void narrow_body(const NarrowArgs<R> &a) {
   allocate(nsel, npair_w, rbase, pbase);
   const bool rec_ok = rbase + nsel <= (unsigned long long)a.cap_active;
   if (nsel && !rec_ok && lane == 0) atomicCAS(&a.st->code, 0, GMCP_E_CAPACITY);
-  if (lane == 0 && tslot >= 0 && a.atile) a.atile[tslot] = tile_id;
+  if (lane == 0 && tslot >= 0) a.atile[tslot] = tile_id;
   if (sel && rec_ok) {
     Rec<R> r;
     r.k = k;
@@ -431,6 +441,18 @@ __device__ __forceinline__ void narrow_body(const NarrowArgs<R> &a) {
     a.pair[pbase + tri_pre + rank] = p;
     atomicAdd(&a.mp_cnt[bM], 1);
   }
+}
+
+template <typename R>
+__device__ __forceinline__ void narrow_body(const NarrowArgs<R> &a) {
+  constexpr int kNW = narrow_waves<R>();
+  __shared__ NarrowLds<R> lds;
+  const int w = threadIdx.x / kWave, count = *a.ntile_cnt, nb = (count + kNW - 1) / kNW;
+  // (one turn per block and a block per tile of the mesh: a loop over the
+  // list holds registers that the turn needs and spills)
+  if (blockIdx.x >= 8 * ((nb + 7) >> 3)) return;
+  const int e = xcd_entry(blockIdx.x, nb), i = e * kNW + w;
+  if (e >= 0) narrow_tile<R>(a, lds, i < count ? a.ntile[i] : -1);
 }
 
 // float: six waves per SIMD (80 registers), three blocks of 8 waves per CU
@@ -604,8 +626,9 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
   __shared__ int32_t candM[kWave];                     // master triangle of each candidate lane
   __shared__ R pacc[18][kWave];                        // each candidate lane's pair sums (mm 6, sm 9, gm 3)
   const int lane = threadIdx.x;
-  const int tile_id = xcd_block(blockIdx.x, gridDim.x);
-  if (tile_id >= a.n_tiles) return;
+  const int count = *a.ntile_cnt, entry = blockIdx.x < 8 * ((count + 7) >> 3) ? xcd_entry(blockIdx.x, count) : -1;
+  if (entry < 0) return;
+  const int tile_id = a.ntile[entry];
   const Tile tl = a.tiles[tile_id];
   const EnvInfo &ev = a.env[tl.env];
   const R dhat = (R)ev.dhat, kappa = (R)ev.kappa, deltaT = (R)ev.delta_T;
@@ -1071,11 +1094,14 @@ __global__ void k_pair_bucket(const Pair<R> *__restrict__ pair, const DevStatus 
     for (int64_t i = p; i <= Tm; i += (int64_t)gridDim.x * blockDim.x) mp_cnt[i] = 0;
     return;
   }
-  if (p >= np) return;
-  int M = pair[p].M;
-  int slot = mp_off[M] + atomicSub(&mp_cnt[M], 1) - 1;
-  mp_key[slot] = ((long long)pair[p].T << 32) | (long long)p;
+  for (; p < np; p += (int64_t)gridDim.x * blockDim.x) {
+    const int M = pair[p].M;
+    const int slot = mp_off[M] + atomicSub(&mp_cnt[M], 1) - 1;
+    mp_key[slot] = ((long long)pair[p].T << 32) | (long long)p;
+  }
 }
+
+constexpr int kPairBlocks = 4096;  // grid of the walks over the pairs at most
 
 // deterministic order inside each bucket: every key is ranked among its
 // bucket's keys (slave triangle, unique per bucket) and written in place
@@ -1085,12 +1111,14 @@ __global__ void k_bucket_rank(const Pair<R> *__restrict__ pair, const int32_t *_
                               const DevStatus *st, int64_t cap_pairs) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t np = (int64_t)st->n_pairs;
-  if (np > cap_pairs || i >= np) return;
-  long long key = mp_key[i];
-  int M = pair[key & 0xffffffffLL].M;
-  int b = mp_off[M], e = mp_off[M + 1], r = 0;
-  for (int j = b; j < e; ++j) r += mp_key[j] < key;
-  mp_list[b + r] = (int32_t)(key & 0xffffffffLL);
+  if (np > cap_pairs) return;
+  for (; i < np; i += (int64_t)gridDim.x * blockDim.x) {
+    const long long key = mp_key[i];
+    const int M = pair[key & 0xffffffffLL].M;
+    int b = mp_off[M], e = mp_off[M + 1], r = 0;
+    for (int j = b; j < e; ++j) r += mp_key[j] < key;
+    mp_list[b + r] = (int32_t)(key & 0xffffffffLL);
+  }
 }
 
 template <typename R>
@@ -1760,7 +1788,9 @@ __global__ __launch_bounds__(kThreads) void k_grad(RowArgs<R> a, const R *__rest
 template <typename R>
 // per-environment sum of the tile energies: a fixed split over 1024
 // threads, wave butterflies, then the 16 wave sums in order (deterministic)
-__global__ __launch_bounds__(1024) void k_energy(const double *__restrict__ tile_E, const EnvInfo *__restrict__ env,
+__global__ __launch_bounds__(1024) void k_energy(const double *__restrict__ tile_E,
+                                                 const uint32_t *__restrict__ tile_act,
+                                                 const uint32_t *__restrict__ epoch, const EnvInfo *__restrict__ env,
                                                  R *energy, const int32_t *__restrict__ row_ptr, int64_t V,
                                                  DevStatus *st, int64_t cap_nnzb) {
   __shared__ double part[1024 / kWave];
@@ -1772,7 +1802,10 @@ __global__ __launch_bounds__(1024) void k_energy(const double *__restrict__ tile
   }
   const int t0 = env[e].tile0, t1 = env[e].tile1;
   double s = 0.0;
-  for (int t = t0 + threadIdx.x; t < t1; t += 1024) s += tile_E[t];
+  // tile_act (nullable): only the tiles the last broad phase listed have an energy
+  const uint32_t now = tile_act ? *epoch : 0;
+  for (int t = t0 + threadIdx.x; t < t1; t += 1024)
+    if (!tile_act || tile_act[t] == now) s += tile_E[t];
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
   if (lane == 0) part[w] = s;
   __syncthreads();
@@ -1995,10 +2028,10 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   na.pair = (Pair<R> *)b.pair;
   na.cap_pairs = c->caps.pairs;
   na.mp_cnt = b.mp_cnt;
-  na.atile = c->mortar ? nullptr : b.atile;  // clipped samples: the step bound walks every tile
+  na.atile = b.atile;  // (clipped samples: the step bound walks every tile)
   na.atile_cnt = b.atile_cnt;
-  na.tile_act = c->mortar ? nullptr : b.tile_act;
-  na.epoch = b.epoch;
+  na.ntile = b.ntile;
+  na.ntile_cnt = b.qcount + 1;
   na.tile_E = b.tile_E;
   na.st = b.status;
   na.features = c->features;
@@ -2008,23 +2041,26 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   prof_mark(c, ST_NARROW, 0);
   if (c->n_tiles) {
     if (c->mortar) {
+      const dim3 mgrid((unsigned)((c->n_tiles + 7) / 8 * 8));
       if constexpr (sizeof(R) == 4)
-        hipLaunchKernelGGL(k_mortar_f32, dim3((unsigned)c->n_tiles), dim3(kWave), 0, s, na);
+        hipLaunchKernelGGL(k_mortar_f32, mgrid, dim3(kWave), 0, s, na);
       else
-        hipLaunchKernelGGL(k_mortar_f64, dim3((unsigned)c->n_tiles), dim3(kWave), 0, s, na);
+        hipLaunchKernelGGL(k_mortar_f64, mgrid, dim3(kWave), 0, s, na);
       hipLaunchKernelGGL(k_mortar_counts, dim3(1), dim3(64), 0, s, b.status);
-    } else
+    } else {
+      const dim3 ngrid((nblk(c->n_tiles, narrow_waves<R>()) + 7) / 8 * 8);
       if constexpr (sizeof(R) == 4)
-        hipLaunchKernelGGL(k_narrow_f32, dim3(nblk(c->n_tiles, narrow_waves<R>())), dim3(kWave * narrow_waves<R>()),
-                           0, s, na);
+        hipLaunchKernelGGL(k_narrow_f32, ngrid, dim3(kWave * narrow_waves<R>()), 0, s, na);
       else
-        hipLaunchKernelGGL(k_narrow_f64, dim3(nblk(c->n_tiles, narrow_waves<R>())), dim3(kWave * narrow_waves<R>()),
-                           0, s, na);
+        hipLaunchKernelGGL(k_narrow_f64, ngrid, dim3(kWave * narrow_waves<R>()), 0, s, na);
+    }
   }
   prof_mark(c, ST_NARROW, 1);
   // bucket pairs by master triangle (needed for master rows and the HVP)
   const Pair<R> *pr = (const Pair<R> *)b.pair;
-  unsigned pb = nblk(c->caps.pairs);
+  // (their number is known on the device only: a grid over the capacity took
+  // 0.13 ms of a 256-environment step starting blocks that found no pair)
+  const unsigned pb = (unsigned)std::min<int64_t>(nblk(c->caps.pairs), kPairBlocks);
   prof_mark(c, ST_BUCKET, 0);
   e = scan_exclusive(c, b.mp_cnt, b.mp_off, c->Tm + 1);  // counts written by the narrow phase
   if (e != hipSuccess) return e;
@@ -2126,7 +2162,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     }
   }
   // per-environment energy (and the BSR's block count when written)
-  hipLaunchKernelGGL(k_energy<R>, dim3(c->n_env), dim3(1024), 0, s, b.tile_E, b.env, energy,
+  hipLaunchKernelGGL(k_energy<R>, dim3(c->n_env), dim3(1024), 0, s, b.tile_E, b.tile_act, b.epoch, b.env, energy,
                      H ? (const int32_t *)H->row_ptr : nullptr, c->V, b.status, H ? H->cap_nnzb : (int64_t)0);
   return hipGetLastError();
 }
@@ -2247,7 +2283,7 @@ hipError_t launch_energy_frozen(gmcp_ctx *c, const R *xs, const R *xm, R *energy
                        c->ts, c->tm, b.tiles, (int)c->n_tiles, b.s_order, b.env, b.rule, (const R *)b.area,
                        (const Rec<R> *)b.rec, b.tri_roff, b.tri_rcnt, (const R *)b.tri_nrm, b.status, c->caps.active,
                        b.tile_E);
-  hipLaunchKernelGGL(k_energy<R>, dim3(c->n_env), dim3(1024), 0, c->stream, b.tile_E, b.env, energy, nullptr,
+  hipLaunchKernelGGL(k_energy<R>, dim3(c->n_env), dim3(1024), 0, c->stream, b.tile_E, nullptr, nullptr, b.env, energy, nullptr,
                      (int64_t)0, b.status, (int64_t)0);
   return hipGetLastError();
 }

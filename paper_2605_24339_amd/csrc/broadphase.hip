@@ -43,7 +43,7 @@ __global__ __launch_bounds__(kBoxThreads) void k_slave_box(const R *__restrict__
                                                          uint32_t *epoch) {
   int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (v == 0) {  // counters of the kernels that follow (nullable), and the broad phase's epoch
-    if (zero_a) *zero_a = 0;
+    if (zero_a) zero_a[0] = zero_a[1] = 0;
     if (zero_b) *zero_b = 0;
     if (epoch) *epoch += 1u;
   }
@@ -346,6 +346,7 @@ __global__ __launch_bounds__(kThreads) void k_query_pre(const R *__restrict__ xs
                                                          int32_t *__restrict__ qcount, uint32_t *__restrict__ box,
                                                          int n_env, DevStatus *st, const uint32_t *__restrict__ epoch,
                                                          uint32_t *__restrict__ tile_act,
+                                                         int32_t *__restrict__ ntile,
                                                          int32_t *__restrict__ tri_npair, int32_t *__restrict__ tri_rcnt,
                                                          int32_t *__restrict__ tri_poff, int32_t *__restrict__ tri_roff) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
@@ -357,6 +358,7 @@ __global__ __launch_bounds__(kThreads) void k_query_pre(const R *__restrict__ xs
     }
   bool active = false;
   int64_t t = -1;
+  int tile = -1;
   float4 fr[3];  // the listed triangle's frame for the query kernel
   if (i < Ts) {
     t = s_order[i];
@@ -447,27 +449,41 @@ __global__ __launch_bounds__(kThreads) void k_query_pre(const R *__restrict__ xs
       tri_roff[t] = 0;
     } else {
       const EnvInfo &ev = env[s_env[t]];
-      tile_act[ev.tile0 + (int)((i - ev.st0) / (kWave / ev.nq))] = *epoch;
+      tile = ev.tile0 + (int)((i - ev.st0) / (kWave / ev.nq));
     }
   }
   // list appends: wave ballots, block prefix in LDS, one atomic per block
-  __shared__ int wq[kThreads / kWave], qb;
+  // and list.  A tile's triangles are consecutive here: the first listed one
+  // in the wave claims the tile with the epoch (the tile may reach into the
+  // next wave), so every tile is listed once.
+  __shared__ int wq[kThreads / kWave], wt[kThreads / kWave], qb, qt;
   const int w = threadIdx.x / kWave;
+  const uint64_t below = (1ull << lane) - 1;
   const uint64_t m = __ballot(active);
-  if (lane == 0) wq[w] = __popcll(m);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int sum = 0;
-    for (int k = 0; k < kThreads / kWave; ++k) {
-      const int c0 = wq[k];
-      wq[k] = sum;
-      sum += c0;
-    }
-    qb = sum ? atomicAdd(qcount, sum) : 0;
+  const int before = __shfl(tile, (m & below) ? 63 - __builtin_clzll(m & below) : lane, kWave);
+  const bool claim = active && (!(m & below) || before != tile) && atomicExch(&tile_act[tile], *epoch) != *epoch;
+  const uint64_t mt = __ballot(claim);
+  if (lane == 0) {
+    wq[w] = __popcll(m);
+    wt[w] = __popcll(mt);
   }
   __syncthreads();
+  if (threadIdx.x == 0) {
+    int sum = 0, tsum = 0;
+    for (int k = 0; k < kThreads / kWave; ++k) {
+      const int c0 = wq[k], c1 = wt[k];
+      wq[k] = sum;
+      wt[k] = tsum;
+      sum += c0;
+      tsum += c1;
+    }
+    qb = sum ? atomicAdd(&qcount[0], sum) : 0;
+    qt = tsum ? atomicAdd(&qcount[1], tsum) : 0;
+  }
+  __syncthreads();
+  if (claim) ntile[qt + wt[w] + __popcll(mt & below)] = tile;
   if (active) {
-    const int slot = qb + wq[w] + __popcll(m & ((1ull << lane) - 1));
+    const int slot = qb + wq[w] + __popcll(m & below);
     qlist[slot] = (int32_t)t;
     for (int k = 0; k < 3; ++k) qrec[3 * (int64_t)slot + k] = fr[k];
   }
@@ -767,7 +783,7 @@ hipError_t launch_broadphase(gmcp_ctx *c, const R *xs, const R *xm) {
     si.which = 1;
     si.box = b.box;
     si.zero[0] = b.qcount;
-    si.nzero[0] = 1;
+    si.nzero[0] = 2;
     si.zero[1] = b.cand_cnt + c->Ts;
     si.nzero[1] = 1;
     if ((e = stage_init(c, si)) != hipSuccess) return e;
@@ -781,7 +797,7 @@ hipError_t launch_broadphase(gmcp_ctx *c, const R *xs, const R *xm) {
     hipLaunchKernelGGL(k_query_pre<R>, dim3(nblk(std::max<int64_t>(c->Ts, c->n_env))), dim3(kThreads), 0, s, xs, c->ts,
                        b.s_order, b.s_env, b.env, b.grid, c->Ts, b.cell_start, c->caps.grid_items, c->total_cells,
                        b.cand_cnt, b.qlist, b.qrec, b.qcount, b.box, c->n_env, b.status, b.epoch, b.tile_act,
-                       b.tri_npair, b.tri_rcnt, b.tri_poff, b.tri_roff);
+                       b.ntile, b.tri_npair, b.tri_rcnt, b.tri_poff, b.tri_roff);
   prof_mark(c, ST_QUERY_PRE, 1);
   // the wave kernels walk the query list with a fixed grid, all of it
   // resident at once

@@ -22,7 +22,7 @@ constexpr int kMaxRule = 4;            // n <= 4  => <= 16 samples per triangle
 constexpr int kRuleDoubles = kMaxRule * 16 * 3 + kMaxRule * 4 * 2;  // 2D rules, then 1D Gauss-Legendre
 constexpr int kGaussOff = kMaxRule * 16 * 3;
 constexpr int kQueryBlocks = 2048;  // largest grid of the list-walking query (its per-block candidate slots)
-constexpr int kTilePerBlock = 4;       // narrow phase: 4 waves, one tile each
+constexpr int kTilePerBlock = 4;       // frozen energy: 4 waves, one tile each
 
 // ---------------------------------------------------------------- status
 struct DevStatus {
@@ -93,7 +93,9 @@ struct Buffers {
   int32_t *cand_cnt, *cand_off, *cand;
   int32_t *cand_tmp, *cand_tmp_off;             // one-pass query: scratch lists and their offsets
   int32_t *cand_blk;                            // [kQueryBlocks] candidates found by each query block
-  int32_t *qlist, *qcount;                      // [Ts], [1]: slave triangles whose prism meets occupied cells
+  int32_t *qlist, *qcount;                      // [Ts], [2]: slave triangles whose prism meets occupied cells;
+                                                //   their number, and that of their work tiles
+  int32_t *ntile;                               // [n_tiles]: the work tiles with a listed triangle
   float4 *qrec;                                 // [Ts][3]: their frames (box lo | T, box hi | env, normal)
   int32_t *slist, *scount;                      // [n_tiles], [1]: work tiles whose swept boxes meet occupied cells
   int32_t *tflag;                               // [n_tiles]: tile listed (zero between calls)

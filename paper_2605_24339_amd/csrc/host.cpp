@@ -202,7 +202,8 @@ size_t plan_workspace(const Sizes &s, const gmcp_caps &cp, char *base, Buffers *
   t.cand_tmp_off = p.take<int32_t>(s.Ts);
   t.cand_blk = p.take<int32_t>(kQueryBlocks);
   t.qlist = p.take<int32_t>(s.Ts);
-  t.qcount = p.take<int32_t>(1);
+  t.qcount = p.take<int32_t>(2);
+  t.ntile = p.take<int32_t>(s.n_tiles);
   t.qrec = p.take<float4>(3 * s.Ts);
   t.slist = p.take<int32_t>(s.n_tiles);
   t.scount = p.take<int32_t>(1);
