@@ -1313,7 +1313,8 @@ __global__ __launch_bounds__(kThreads) void k_row_pre(RowArgs<R> a, int4 *__rest
 // the contributions and the incident triangles' normals are also kept in
 // LDS (rows with more contributions than the stash, or more than kRowSrc
 // incident triangles, re-walk their sources), each lane owns one distinct
-// column and sums its contributions in the canonical order.
+// column and sums its contributions in the canonical order, from a mask of
+// the groups that hold it.
 // Master row j: master columns take the per-master-triangle blocks of
 // k_mtri, summed over the incident triangles in adjacency order; slave
 // columns a are the slave vertices of the pairs of those triangles, and
@@ -1327,15 +1328,18 @@ constexpr int kRowEnt = 512;     // contribution stash of heavy rows (light rows
 constexpr int kRowSrc = 32;
 
 // LDS bytes of one wave of k_rows: hash set (slots, compacted in place),
-// the incident-triangle table, the item marks of one round, and in PASS 1 the contribution stash - in
-// groups of three (a triangle's own vertices, or one pair's master
-// vertices: three distinct columns, the table index, three coefficients) -
-// and the incident triangles' normals; a multiple of 16 bytes
+// the incident-triangle table, the item marks of one round, and in PASS 1
+// the contribution stash - in groups of three (a triangle's own vertices, or
+// one pair's master vertices: three distinct columns, the table index, three
+// coefficients) -, the incident triangles' normals, the place of each slot's
+// column and the masks of 64 columns; a multiple of 16 bytes
+constexpr int kRowMap = 1024;  // slots of a stashed row's set at most (10 bits each in a group)
 template <typename R>
 constexpr size_t row_lds_wave(int slots, int pass, bool heavy, int light_bound) {
   return ((size_t)slots * 4 + (size_t)8 * kRowSrc * 4 + (size_t)kWave * 4 +
-          (pass == 1 ? (size_t)((heavy ? kRowEnt : light_bound) / 3 + 1) * (16 + 3 * sizeof(R)) +
-                           (size_t)kRowSrc * 3 * sizeof(R)
+          (pass == 1 ? (size_t)((heavy ? kRowEnt : light_bound) / 3 + 1) * (8 + 3 * sizeof(R)) +
+                           (size_t)kRowSrc * 3 * sizeof(R) + (size_t)kWave * 8 +
+                           (size_t)(slots < kRowMap ? slots : kRowMap) * 2
                      : 0) +
           15) / 16 * 16;
 }
@@ -1358,9 +1362,11 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
   int32_t *stv = spb + kRowSrc;  // master rows: the triangle's three vertex ids
   int32_t *smk = stv + 3 * kRowSrc;  // per round of 64 items: the table entry whose items start at a lane
   const int gcap = ecap / 3 + 1;
-  int4 *egrp = reinterpret_cast<int4 *>(smk + kWave);  // PASS 1 stash: three columns + table index,
-  R *ecoef = reinterpret_cast<R *>(egrp + gcap);          // three coefficients per group
-  R *snrm = ecoef + 3 * gcap;                             // normals of the table's triangles
+  uint64_t *cmask = reinterpret_cast<uint64_t *>(smk + kWave);  // PASS 1: groups that hold each of 64 columns
+  int2 *egrp = reinterpret_cast<int2 *>(cmask + kWave);         // stash: three slots (10 bits each), table index,
+  R *ecoef = reinterpret_cast<R *>(egrp + gcap);                // three coefficients per group
+  R *snrm = ecoef + 3 * gcap;                                   // normals of the table's triangles
+  uint16_t *smap = reinterpret_cast<uint16_t *>(snrm + 3 * kRowSrc);  // place in `dense` of a slot's column
   if ((pass == 1 || pass == 3) && (int64_t)a.row_ptr[a.V] > a.cap_nnzb) return;
 
   // the table entry owning item f0 + lane (the last entry whose item prefix
@@ -1630,10 +1636,11 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
   bool full = false;
   // one group of three contributions starting at canonical offset e0 (a multiple of 3)
   auto put3 = [&](const int32_t col[3], const R cf[3], int e0, int k) {
-    for (int b = 0; b < 3; ++b) row_slot(key, tsz, col[b], &full);
+    int slot[3];
+    for (int b = 0; b < 3; ++b) slot[b] = row_slot(key, tsz, col[b], &full);
     if (stash) {
       const int gi = e0 / 3;
-      egrp[gi] = make_int4(col[0], col[1], col[2], k);
+      egrp[gi] = make_int2(slot[0] | slot[1] << 10 | slot[2] << 20, k);
       for (int b = 0; b < 3; ++b) ecoef[3 * gi + b] = cf[b];
     }
   };
@@ -1703,7 +1710,11 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
     const int32_t kv = i < tsz ? key[i] : -1;  // read before any lane writes (in place)
     const bool used = kv >= 0;
     const uint64_t m = __ballot(used);
-    if (used) dense[nuniq + __popcll(m & ((1ull << lane) - 1))] = kv;
+    if (used) {
+      const int u = nuniq + __popcll(m & ((1ull << lane) - 1));
+      dense[u] = kv;
+      if (stash) smap[i] = (uint16_t)u;
+    }
     nuniq += __popcll(m);
   }
   if (pass == 0) {
@@ -1711,10 +1722,17 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
     return;
   }
   wave_sync();
-  for (int u = lane; u < nuniq; u += kWave) {
-    const int32_t c = dense[u];
-    int r = 0;
-    for (int m = 0; m < nuniq; ++m) r += dense[m] < c;
+  const int ng = n_ent / 3;
+  if (stash) {  // the groups' slots to the places of their columns
+    for (int g = lane; g < ng; g += kWave) {
+      const int p = egrp[g].x;
+      egrp[g].x = smap[p & 1023] | smap[(p >> 10) & 1023] << 10 | smap[(p >> 20) & 1023] << 20;
+    }
+    wave_sync();
+  }
+  for (int u0 = 0; u0 < nuniq; u0 += kWave) {
+    const int u = u0 + lane;
+    const int32_t c = u < nuniq ? dense[u] : -1;
     R v[6] = {0, 0, 0, 0, 0, 0};
     auto add_n = [&](R cf, const R *nn) {
       v[0] += cf * nn[0] * nn[0];
@@ -1724,18 +1742,41 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
       v[4] += cf * nn[1] * nn[2];
       v[5] += cf * nn[2] * nn[2];
     };
-    if (stash) {  // the three columns of a group are distinct: at most one matches
-      for (int gi = 0; gi < n_ent / 3; ++gi) {
-        const int4 cg = egrp[gi];
-        const int b = cg.x == c ? 0 : (cg.y == c ? 1 : (cg.z == c ? 2 : -1));
-        if (b >= 0) add_n(ecoef[3 * gi + b], snrm + 3 * cg.w);
+    if (stash) {
+      // Every group marks its columns among these 64 (its three columns are
+      // distinct, so a bit per group is enough), then a lane adds the groups
+      // of its column only, in canonical order: two or three in the mean.
+      // (All lanes looking at every group was most of the pass's instructions.)
+      for (int g0 = 0; g0 < ng; g0 += kWave) {
+        cmask[lane] = 0;
+        wave_sync();
+        if (g0 + lane < ng) {
+          const int p = egrp[g0 + lane].x;
+          for (int b = 0; b < 3; ++b) {
+            const int q = ((p >> (10 * b)) & 1023) - u0;
+            if (q >= 0 && q < kWave)
+              atomicOr(reinterpret_cast<unsigned long long *>(&cmask[q]), 1ull << lane);
+          }
+        }
+        wave_sync();
+        for (uint64_t bits = cmask[lane]; bits; bits &= bits - 1) {
+          const int g = g0 + __ffsll((unsigned long long)bits) - 1;
+          const int2 cg = egrp[g];
+          const int b = (cg.x & 1023) == u ? 0 : (((cg.x >> 10) & 1023) == u ? 1 : 2);
+          add_n(ecoef[3 * g + b], snrm + 3 * cg.y);
+        }
+        wave_sync();  // the masks are cleared next
       }
-    } else {
+    }
+    if (u >= nuniq) continue;
+    if (!stash) {
       for (int src = sb; src < se; ++src)
         visit_src(src, [&](int32_t col, R cf, int t) {
           if (col == c) add_n(cf, a.tri_nrm + 3 * (int64_t)t);
         });
     }
+    int r = 0;
+    for (int m = 0; m < nuniq; ++m) r += dense[m] < c;
     const int64_t dst = (int64_t)a.row_ptr[row] + r;
     a.col[dst] = c;
     R *ov = a.val + 9 * dst;
