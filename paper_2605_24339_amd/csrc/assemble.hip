@@ -1145,23 +1145,50 @@ struct RowArgs {
   int light_bound;  // column insertions of a light row (32, 64, 128 or 256)
 };
 
-constexpr int kRowWaves = 2;
+constexpr int kRowWaves = 2;   // light rows
+// heavy rows, one wave per block: two waves in each of the default blocks
+// held nearly all LDS of the card while the light rows ran beside them (256
+// environments, step: 5.97 ms, with half as many 5.71)
+constexpr int kHeavyWaves = 1;
 // the list-walking row kernels use fixed grids, by default many times the
 // blocks resident at once (kDefaultRowBlocks light, kDefaultHeavyBlocks
 // heavy): a block's share of the list is short, so blocks that start late
 // (the device is shared with the other stream's kernels) finish soon after
 // the rest
 
-// slot of column `col` in an open-addressing table of `slots` (power of 2)
-__device__ inline int row_slot(int32_t *key, int slots, int32_t col, bool *full) {
-  uint32_t h = ((uint32_t)col * 2654435761u) & (uint32_t)(slots - 1);
+// The distinct columns of a row are kept in an open-addressing table of
+// `slots` (a power of 2) in LDS, free entries -1.
+// slots of three columns, their probes in flight together (one after the
+// other the LDS round trips were a third of a short row's time)
+__device__ inline void row_slot3(int32_t *key, int slots, const int32_t col[3], int slot[3], bool *full) {
+  const uint32_t mask = (uint32_t)(slots - 1);
+  uint32_t h[3];
+  bool open[3] = {true, true, true};
+#pragma unroll
+  for (int b = 0; b < 3; ++b) h[b] = ((uint32_t)col[b] * 2654435761u) & mask;
   for (int probe = 0; probe < slots; ++probe) {
-    int32_t prev = atomicCAS(&key[h], -1, col);
-    if (prev == -1 || prev == col) return (int)h;
-    h = (h + 1) & (uint32_t)(slots - 1);
+    int32_t prev[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) prev[b] = open[b] ? atomicCAS(&key[h[b]], -1, col[b]) : col[b];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      open[b] = prev[b] != -1 && prev[b] != col[b];
+      if (open[b]) h[b] = (h[b] + 1) & mask;
+    }
+    if (!(open[0] || open[1] || open[2])) break;
   }
-  *full = true;
-  return -1;
+  for (int b = 0; b < 3; ++b) slot[b] = (int)h[b];
+  if (open[0] || open[1] || open[2]) *full = true;
+}
+
+// number of columns below c among the n4 * 4 of a compacted set (16-byte aligned)
+__device__ inline int row_rank(const int32_t *dense, int n4, int32_t c) {
+  int r = 0;
+  for (int m = 0; m < n4; ++m) {
+    const int4 q = reinterpret_cast<const int4 *>(dense)[m];
+    r += (q.x < c) + (q.y < c) + (q.z < c) + (q.w < c);
+  }
+  return r;
 }
 
 // Four lanes per master triangle with contact pairs: the sum over its pairs
@@ -1321,6 +1348,13 @@ __global__ __launch_bounds__(kThreads) void k_row_pre(RowArgs<R> a, int4 *__rest
 // their blocks equal block (a, j) of slave row a (each contribution is a
 // symmetric coef n n^T), so PASS 3 copies them after PASS 1 has written the
 // slave rows.  Columns are ranked and written ascending.
+//
+// What bounds it: the light rows of a batch the instructions of their hash
+// probes and rankings, a heavy row and a small scene the chain of one row
+// (LDS round trips of the probes, the blocks' loads).  256 environments,
+// f32, 561 k rows: fill 1.05 ms light with 0.63 ms heavy beside it (before
+// the masks, the three probes together and the blocks two at a time 1.30 and
+// 1.55), count 0.36 and 0.22 ms.
 constexpr int kRowEnt = 512;     // contribution stash of heavy rows (light rows: their bound)
 // incident triangles of a row taken per chunk (kept in LDS): a vertex has
 // far fewer than 32 in the common case, and the smaller table lets more
@@ -1495,7 +1529,7 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
     const bool one_chunk = se - sb <= kRowSrc;
     for (int s0 = sb; s0 < se; s0 += kRowSrc) {
       const int src = s0 + lane;
-      int t = 0, corner = 0, np = 0, pb = 0, tv[3] = {0, 0, 0};
+      int t = 0, corner = 0, np = 0, pb = 0, tv[3] = {-1, -1, -1};  // -1: no pairs (no contribution)
       if (lane < kRowSrc && src < se) {
         const int ent = vt_at(src);
         t = ent >> 2;
@@ -1511,7 +1545,7 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
       wave_sync();  // the previous chunk's table reads are done
       if (lane < kRowSrc) {
         sip[lane] = iin - nit;
-        stt[lane] = np > 0 ? t : -1;  // -1: no pairs (no contribution)
+        stt[lane] = t;
         sco[lane] = corner;
         spb[lane] = pb;
         for (int m = 0; m < 3; ++m) stv[3 * lane + m] = tv[m];
@@ -1521,12 +1555,15 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
         const int lo = owner(f0, iin - nit, nit, carry), f = f0 + lane;
         if (f >= items) continue;
         const int j = f - sip[lo];
+        int32_t col[3];
+        int slot[3];
         if (j == 0) {
-          for (int m = 0; m < 3; ++m) row_slot(key, tsz, (int32_t)(a.Vs + stv[3 * lo + m]), &full);
+          for (int m = 0; m < 3; ++m) col[m] = (int32_t)(a.Vs + stv[3 * lo + m]);
         } else {
           const int64_t T = a.mp_key[spb[lo] + j - 1] >> 32;
-          for (int q = 0; q < 3; ++q) row_slot(key, tsz, a.ts[3 * T + q], &full);
+          for (int q = 0; q < 3; ++q) col[q] = a.ts[3 * T + q];
         }
+        row_slot3(key, tsz, col, slot, &full);
       }
     }
     if (__any(full)) {
@@ -1545,31 +1582,56 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
       const int32_t kv = i < tsz ? key[i] : -1;  // read before any lane writes (in place)
       const bool used = kv >= 0;
       const uint64_t m = __ballot(used);
-      if (used) dense[nuniq + __popcll(m & ((1ull << lane) - 1))] = kv;
+      if (pass != 0 && used) dense[nuniq + __popcll(m & ((1ull << lane) - 1))] = kv;
       nuniq += __popcll(m);
     }
     if (pass == 0) {
       if (lane == 0) a.row_cnt[row] = nuniq;
       return;
     }
+    const int n4 = (nuniq + 3) >> 2;
+    if (nuniq + lane < 4 * n4) dense[nuniq + lane] = INT32_MAX;
     wave_sync();
     for (int u = lane; u < nuniq; u += kWave) {
       const int32_t c = dense[u];
-      int r = 0;
-      for (int m = 0; m < nuniq; ++m) r += dense[m] < c;
+      const int r = row_rank(dense, n4, c);
       const int64_t dst = (int64_t)a.row_ptr[row] + r;
       a.col[dst] = c;
       if (c < a.Vs) continue;  // slave column: PASS 3
       R v[6] = {0, 0, 0, 0, 0, 0};
       if (one_chunk) {  // the incident triangles are in the table, in adjacency order
-        for (int k = 0; k < se - sb; ++k) {
-          const int t = stt[k];
-          if (t < 0) continue;
-          for (int m = 0; m < 3; ++m) {
-            if ((int32_t)(a.Vs + stv[3 * k + m]) != c) continue;
-            const R *B = a.mtri + 45 * (int64_t)t + 6 * sym3(sco[k], m);
-            for (int z = 0; z < 6; ++z) v[z] += B[z];
+        // the (triangle, vertex) entries that are this column - two for a
+        // neighbour, all triangles for the row's own - as a mask first, then
+        // their blocks two at a time: a load per entry looked at, one after
+        // the other, was most of a short row's time
+        const int32_t vc = (int32_t)(c - a.Vs);
+        uint64_t m0 = 0;
+        uint32_t m1 = 0;
+        for (int q = 0; 4 * q < 3 * (se - sb); ++q) {
+          const int4 tv = reinterpret_cast<const int4 *>(stv)[q];
+          const uint64_t four = (uint64_t)((tv.x == vc) | (tv.y == vc) << 1 | (tv.z == vc) << 2 | (tv.w == vc) << 3);
+          if (q < 16) m0 |= four << (4 * q);
+          else m1 |= (uint32_t)four << (4 * (q - 16));
+        }
+        auto next = [&]() -> const R * {  // the block of the lowest entry left
+          const int e = m0 ? __ffsll((unsigned long long)m0) - 1 : 63 + __ffs((int)m1);
+          if (m0) m0 &= m0 - 1;
+          else m1 &= m1 - 1;
+          const int k = e / 3;
+          return a.mtri + 45 * (int64_t)stt[k] + 6 * sym3(sco[k], e - 3 * k);
+        };
+        while (m0 | m1) {
+          const R *A = next();
+          const bool two = (m0 | m1) != 0;
+          const R *B = two ? next() : A;
+          R va[6], vb[6];
+          for (int z = 0; z < 6; ++z) {
+            va[z] = A[z];
+            vb[z] = B[z];
           }
+          for (int z = 0; z < 6; ++z) v[z] += va[z];
+          if (two)
+            for (int z = 0; z < 6; ++z) v[z] += vb[z];
         }
       } else {
         for (int src = sb; src < se; ++src) {
@@ -1637,7 +1699,7 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
   // one group of three contributions starting at canonical offset e0 (a multiple of 3)
   auto put3 = [&](const int32_t col[3], const R cf[3], int e0, int k) {
     int slot[3];
-    for (int b = 0; b < 3; ++b) slot[b] = row_slot(key, tsz, col[b], &full);
+    row_slot3(key, tsz, col, slot, &full);
     if (stash) {
       const int gi = e0 / 3;
       egrp[gi] = make_int2(slot[0] | slot[1] << 10 | slot[2] << 20, k);
@@ -1710,7 +1772,7 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
     const int32_t kv = i < tsz ? key[i] : -1;  // read before any lane writes (in place)
     const bool used = kv >= 0;
     const uint64_t m = __ballot(used);
-    if (used) {
+    if (pass != 0 && used) {
       const int u = nuniq + __popcll(m & ((1ull << lane) - 1));
       dense[u] = kv;
       if (stash) smap[i] = (uint16_t)u;
@@ -1721,6 +1783,8 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
     if (lane == 0) a.row_cnt[row] = nuniq;
     return;
   }
+  const int n4 = (nuniq + 3) >> 2;
+  if (nuniq + lane < 4 * n4) dense[nuniq + lane] = INT32_MAX;
   wave_sync();
   const int ng = n_ent / 3;
   if (stash) {  // the groups' slots to the places of their columns
@@ -1775,8 +1839,7 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
           if (col == c) add_n(cf, a.tri_nrm + 3 * (int64_t)t);
         });
     }
-    int r = 0;
-    for (int m = 0; m < nuniq; ++m) r += dense[m] < c;
+    const int r = row_rank(dense, n4, c);
     const int64_t dst = (int64_t)a.row_ptr[row] + r;
     a.col[dst] = c;
     R *ov = a.val + 9 * dst;
@@ -2153,7 +2216,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   if (grad && !H) {  // gradient alone: the row kernel's gradient-only pass
     prof_mark(c, ST_GRAD, 0);
     if ((e = fork()) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_rows<R, 2, true>), hgrid, dim3(kWave * nw), 0, hs, ra, 64, heavy, nheavy);
+    hipLaunchKernelGGL((k_rows<R, 2, true>), hgrid, dim3(kWave * kHeavyWaves), 0, hs, ra, 64, heavy, nheavy);
     hipLaunchKernelGGL((k_rows<R, 2, false>), rgrid, dim3(kWave * nw), 0, s, ra, 64, light, nlight);
     if ((e = join()) != hipSuccess) return e;
     prof_mark(c, ST_GRAD, 1);
@@ -2168,14 +2231,14 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     int hslots = 512;
     while (hslots < c->caps.row_entries && hslots < 4096) hslots <<= 1;
     auto lds = [&](int sl, int pass, bool heavy) {
-      return (size_t)nw * row_lds_wave<R>(sl, pass, heavy, ra.light_bound);
+      return (size_t)(heavy ? kHeavyWaves : nw) * row_lds_wave<R>(sl, pass, heavy, ra.light_bound);
     };
     if ((e = fork()) != hipSuccess) return e;
-    if (sums) mtri(hs);  // read by the writing pass
     prof_mark(c, ST_ROWS_COUNT_H, 0);
-    hipLaunchKernelGGL((k_rows<R, 0, true>), hgrid, dim3(kWave * nw), lds(hslots, 0, true), hs, ra, hslots, heavy,
+    hipLaunchKernelGGL((k_rows<R, 0, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 0, true), hs, ra, hslots, heavy,
                        nheavy);
     prof_mark(c, ST_ROWS_COUNT_H, 1);
+    if (sums) mtri(hs);  // read by the writing pass
     prof_mark(c, ST_ROWS_COUNT, 0);
     hipLaunchKernelGGL((k_rows<R, 0, false>), rgrid, dim3(kWave * nw), lds(lslots, 0, false), s, ra, lslots, light,
                        nlight);
@@ -2185,7 +2248,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     if (e != hipSuccess) return e;
     if ((e = fork()) != hipSuccess) return e;
     prof_mark(c, ST_ROWS_FILL_H, 0);
-    hipLaunchKernelGGL((k_rows<R, 1, true>), hgrid, dim3(kWave * nw), lds(hslots, 1, true), hs, ra, hslots, heavy,
+    hipLaunchKernelGGL((k_rows<R, 1, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 1, true), hs, ra, hslots, heavy,
                        nheavy);
     prof_mark(c, ST_ROWS_FILL_H, 1);
     prof_mark(c, ST_ROWS_FILL, 0);
@@ -2196,7 +2259,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     if (c->V > c->Vs) {
       prof_mark(c, ST_ROWS_COPY, 0);
       if ((e = fork()) != hipSuccess) return e;
-      hipLaunchKernelGGL((k_rows<R, 3, true>), hgrid, dim3(kWave * nw), 0, hs, ra, hslots, heavy, nheavy);
+      hipLaunchKernelGGL((k_rows<R, 3, true>), hgrid, dim3(kWave * kHeavyWaves), 0, hs, ra, hslots, heavy, nheavy);
       hipLaunchKernelGGL((k_rows<R, 3, false>), rgrid, dim3(kWave * nw), 0, s, ra, lslots, light, nlight);
       if ((e = join()) != hipSuccess) return e;
       prof_mark(c, ST_ROWS_COPY, 1);
