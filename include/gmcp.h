@@ -284,7 +284,11 @@ int gmcp_ccd_step(gmcp_ctx *ctx, const void *x_slave, const void *x_master, cons
  * second stream; it must not overlap another step-bound call.
  * gmcp_ccd_finish returns GMCP_E_ARG unless gmcp_ccd_swept was called since
  * the last bound (host order) and an assembly exists.
+ * gmcp_wait_samples makes the context's stream wait for the sample records of
+ * the last gmcp_assemble only, not for its rows: gmcp_ccd_finish on a second
+ * stream after it overlaps the row kernels (GMCP_E_ARG without an assembly).
  */
+int gmcp_wait_samples(gmcp_ctx *ctx);
 int gmcp_ccd_swept(gmcp_ctx *ctx, const void *x_slave, const void *x_master, const void *dx_slave,
                    const void *dx_master);
 int gmcp_ccd_finish(gmcp_ctx *ctx, const void *dx_slave, const void *dx_master, void *alpha);

@@ -1254,6 +1254,53 @@ __global__ __launch_bounds__(kThreads) void k_mtri(const Pair<R> *__restrict__ p
   for (int z = 0; z < 9; ++z) out[36 + z] = g[z];
 }
 
+// Energy of environment e from its tiles: a fixed split over 1024 partial
+// sums (NT threads hold 1024 / NT each), wave butterflies over 64 of them,
+// then the 16 sums in order: the same value for every NT, on every run.
+template <typename R>
+struct EnergyArgs {
+  const double *tile_E;
+  const uint32_t *tile_act, *epoch;  // tile_act (nullable): only the tiles the last broad phase listed have an energy
+  const EnvInfo *env;
+  R *energy;
+};
+
+template <typename R, int NT>
+__device__ inline void env_energy(const EnergyArgs<R> &a, int e) {
+  constexpr int kParts = 1024 / kWave;
+  __shared__ double part[kParts];
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  const int t0 = a.env[e].tile0, t1 = a.env[e].tile1;
+  const uint32_t now = a.tile_act ? *a.epoch : 0;
+  constexpr int kV = 1024 / NT;
+  double s[kV] = {};
+  for (int tb = t0 + threadIdx.x; tb < t1; tb += 2 * 1024) {
+    // up to 2 kV tiles of the thread, their loads in flight together
+    uint32_t act[2 * kV];
+    double E[2 * kV];
+#pragma unroll
+    for (int v = 0; v < 2 * kV; ++v) {
+      const int t = min(tb + v * NT, t1 - 1);
+      act[v] = a.tile_act ? a.tile_act[t] : now;
+      E[v] = a.tile_E[t];
+    }
+#pragma unroll
+    for (int v = 0; v < 2 * kV; ++v)
+      if (tb + v * NT < t1 && act[v] == now) s[v % kV] += E[v];
+  }
+#pragma unroll
+  for (int v = 0; v < kV; ++v) {
+    for (int o = 32; o > 0; o >>= 1) s[v] += __shfl_xor(s[v], o, kWave);
+    if (lane == 0) part[v * (NT / kWave) + w] = s[v];
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double tot = 0.0;
+    for (int k = 0; k < kParts; ++k) tot += part[k];
+    a.energy[e] = (R)tot;
+  }
+}
+
 // Thread per BSR row: counts the row's contributions (the entries the row
 // kernel enumerates).  Rows without any get their count and gradient zeroed
 // here; the others are listed for the wave kernels - light rows (at most
@@ -1263,10 +1310,14 @@ __global__ __launch_bounds__(kThreads) void k_mtri(const Pair<R> *__restrict__ p
 // pair records overflowed.  A light row has at most a.light_bound column
 // insertions (a power of two); its column table has 2 a.light_bound slots
 // and the hash tables inside it grow in powers of two up to that size.
-
 template <typename R>
 __global__ __launch_bounds__(kThreads) void k_row_pre(RowArgs<R> a, int4 *__restrict__ rlist,
-                                                       int32_t *__restrict__ rcount, int zero_cnt) {
+                                                       int32_t *__restrict__ rcount, int zero_cnt,
+                                                       EnergyArgs<R> en, int row_blocks) {
+  if ((int)blockIdx.x >= row_blocks) {
+    env_energy<R, kThreads>(en, blockIdx.x - row_blocks);
+    return;
+  }
   const int64_t row = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   const int lane = threadIdx.x & (kWave - 1);
   int n_ent = 0, sb = 0, se = 0;
@@ -1401,7 +1452,14 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
   R *ecoef = reinterpret_cast<R *>(egrp + gcap);                // three coefficients per group
   R *snrm = ecoef + 3 * gcap;                                   // normals of the table's triangles
   uint16_t *smap = reinterpret_cast<uint16_t *>(snrm + 3 * kRowSrc);  // place in `dense` of a slot's column
-  if ((pass == 1 || pass == 3) && (int64_t)a.row_ptr[a.V] > a.cap_nnzb) return;
+  if (pass == 1 || pass == 3) {
+    const int64_t nnzb = a.row_ptr[a.V];
+    if (pass == 1 && !HEAVY && blockIdx.x == 0 && threadIdx.x == 0) {  // the BSR's block count
+      a.st->nnzb = (unsigned long long)nnzb;
+      if (nnzb > a.cap_nnzb) atomicCAS(&a.st->code, 0, GMCP_E_CAPACITY);
+    }
+    if (nnzb > a.cap_nnzb) return;
+  }
 
   // the table entry owning item f0 + lane (the last entry whose item prefix
   // is <= it): each entry with items marks the lane of its first item, a
@@ -1890,36 +1948,9 @@ __global__ __launch_bounds__(kThreads) void k_grad(RowArgs<R> a, const R *__rest
 }
 
 template <typename R>
-// per-environment sum of the tile energies: a fixed split over 1024
-// threads, wave butterflies, then the 16 wave sums in order (deterministic)
-__global__ __launch_bounds__(1024) void k_energy(const double *__restrict__ tile_E,
-                                                 const uint32_t *__restrict__ tile_act,
-                                                 const uint32_t *__restrict__ epoch, const EnvInfo *__restrict__ env,
-                                                 R *energy, const int32_t *__restrict__ row_ptr, int64_t V,
-                                                 DevStatus *st, int64_t cap_nnzb) {
-  __shared__ double part[1024 / kWave];
-  const int e = blockIdx.x, lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  if (row_ptr && e == 0 && threadIdx.x == 0) {  // the BSR's block count (after the row kernels)
-    const long long nnzb = row_ptr[V];
-    st->nnzb = (unsigned long long)nnzb;
-    if (nnzb > cap_nnzb) atomicCAS(&st->code, 0, GMCP_E_CAPACITY);
-  }
-  const int t0 = env[e].tile0, t1 = env[e].tile1;
-  double s = 0.0;
-  // tile_act (nullable): only the tiles the last broad phase listed have an energy
-  const uint32_t now = tile_act ? *epoch : 0;
-  for (int t = t0 + threadIdx.x; t < t1; t += 1024)
-    if (!tile_act || tile_act[t] == now) s += tile_E[t];
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
-  if (lane == 0) part[w] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double tot = 0.0;
-    for (int k = 0; k < 1024 / kWave; ++k) tot += part[k];
-    energy[e] = (R)tot;
-  }
+__global__ __launch_bounds__(1024) void k_energy(EnergyArgs<R> a) {
+  env_energy<R, 1024>(a, blockIdx.x);
 }
-
 
 template <typename R>
 __global__ void k_rest_area(const R *__restrict__ x, const int32_t *__restrict__ ts, int64_t Ts, R *area,
@@ -2160,6 +2191,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     }
   }
   prof_mark(c, ST_NARROW, 1);
+  if ((e = hipEventRecord(c->ev_samples, s)) != hipSuccess) return e;  // gmcp_wait_samples
   // bucket pairs by master triangle (needed for master rows and the HVP)
   const Pair<R> *pr = (const Pair<R> *)b.pair;
   // (their number is known on the device only: a grid over the capacity took
@@ -2186,10 +2218,11 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     hipError_t r = hipEventRecord(c->ev_fork, s);
     return r != hipSuccess ? r : hipStreamWaitEvent(c->side, c->ev_fork, 0);
   };
+  auto mark_side = [&]() { return par ? hipEventRecord(c->ev_join, c->side) : hipSuccess; };
+  auto wait_side = [&]() { return par ? hipStreamWaitEvent(s, c->ev_join, 0) : hipSuccess; };
   auto join = [&]() {
-    if (!par) return hipSuccess;
-    hipError_t r = hipEventRecord(c->ev_join, c->side);
-    return r != hipSuccess ? r : hipStreamWaitEvent(s, c->ev_join, 0);
+    const hipError_t r = mark_side();
+    return r != hipSuccess ? r : wait_side();
   };
   const bool sums = !c->kinematic && (grad || H) && c->Tm;
   auto mtri = [&](hipStream_t st) {
@@ -2199,10 +2232,14 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     prof_mark(c, ST_MTRI, 1);
   };
   if (sums && !H) mtri(s);  // the gradient rows read the sums
+  // the energies in blocks of the row lists' kernel (one launch less in the
+  // chain, 7 us of a small step)
+  const EnergyArgs<R> en{b.tile_E, b.tile_act, b.epoch, b.env, energy};
   if (grad || H) {
     prof_mark(c, ST_ROWS_PRE, 0);
     if (c->V)
-      hipLaunchKernelGGL(k_row_pre<R>, dim3(nblk(c->V)), dim3(kThreads), 0, s, ra, b.rlist, b.rcount, H ? 1 : 0);
+      hipLaunchKernelGGL(k_row_pre<R>, dim3(nblk(c->V) + c->n_env), dim3(kThreads), 0, s, ra, b.rlist, b.rcount,
+                         H ? 1 : 0, en, (int)nblk(c->V));
     prof_mark(c, ST_ROWS_PRE, 1);
   }
   // the row kernels walk the two row lists with fixed grids: light rows with
@@ -2238,15 +2275,17 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     hipLaunchKernelGGL((k_rows<R, 0, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 0, true), hs, ra, hslots, heavy,
                        nheavy);
     prof_mark(c, ST_ROWS_COUNT_H, 1);
-    if (sums) mtri(hs);  // read by the writing pass
+    if ((e = mark_side()) != hipSuccess) return e;
+    if (sums) mtri(hs);  // read by the writing pass, beside the scan
     prof_mark(c, ST_ROWS_COUNT, 0);
     hipLaunchKernelGGL((k_rows<R, 0, false>), rgrid, dim3(kWave * nw), lds(lslots, 0, false), s, ra, lslots, light,
                        nlight);
     prof_mark(c, ST_ROWS_COUNT, 1);
-    if ((e = join()) != hipSuccess) return e;
+    if ((e = wait_side()) != hipSuccess) return e;
     e = scan_exclusive(c, b.row_cnt, H->row_ptr, c->V + 1);
     if (e != hipSuccess) return e;
     if ((e = fork()) != hipSuccess) return e;
+    if (sums && (e = join()) != hipSuccess) return e;  // the sums
     prof_mark(c, ST_ROWS_FILL_H, 0);
     hipLaunchKernelGGL((k_rows<R, 1, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 1, true), hs, ra, hslots, heavy,
                        nheavy);
@@ -2265,9 +2304,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
       prof_mark(c, ST_ROWS_COPY, 1);
     }
   }
-  // per-environment energy (and the BSR's block count when written)
-  hipLaunchKernelGGL(k_energy<R>, dim3(c->n_env), dim3(1024), 0, s, b.tile_E, b.tile_act, b.epoch, b.env, energy,
-                     H ? (const int32_t *)H->row_ptr : nullptr, c->V, b.status, H ? H->cap_nnzb : (int64_t)0);
+  if (!(grad || H) || !c->V) hipLaunchKernelGGL(k_energy<R>, dim3(c->n_env), dim3(1024), 0, s, en);
   return hipGetLastError();
 }
 
@@ -2387,8 +2424,8 @@ hipError_t launch_energy_frozen(gmcp_ctx *c, const R *xs, const R *xm, R *energy
                        c->ts, c->tm, b.tiles, (int)c->n_tiles, b.s_order, b.env, b.rule, (const R *)b.area,
                        (const Rec<R> *)b.rec, b.tri_roff, b.tri_rcnt, (const R *)b.tri_nrm, b.status, c->caps.active,
                        b.tile_E);
-  hipLaunchKernelGGL(k_energy<R>, dim3(c->n_env), dim3(1024), 0, c->stream, b.tile_E, nullptr, nullptr, b.env, energy, nullptr,
-                     (int64_t)0, b.status, (int64_t)0);
+  const EnergyArgs<R> en{b.tile_E, nullptr, nullptr, b.env, energy};
+  hipLaunchKernelGGL(k_energy<R>, dim3(c->n_env), dim3(1024), 0, c->stream, en);
   return hipGetLastError();
 }
 

@@ -174,6 +174,7 @@ struct gmcp_ctx {
   // graph capture); null if creation failed (then everything runs in order)
   hipStream_t side;
   hipEvent_t ev_fork, ev_join;
+  hipEvent_t ev_samples;  // the last assembly's sample records are written
   bool f64, kinematic, mortar, features;
   int n_env;
   int64_t Vs, Vm, Ts, Tm, Ns, V, n_tiles, total_cells;

@@ -518,12 +518,18 @@ int gmcp_create(gmcp_ctx **out, const gmcp_layout *L, const gmcp_caps *caps, con
   } else {
     c->side = nullptr;
   }
+  if (hipEventCreateWithFlags(&c->ev_samples, hipEventDisableTiming) != hipSuccess) {
+    c->ev_samples = nullptr;
+    gmcp_destroy(c);
+    return GMCP_E_HIP;
+  }
   *out = c;
   return GMCP_OK;
 }
 
 void gmcp_destroy(gmcp_ctx *c) {
   if (!c) return;
+  if (c->ev_samples) (void)hipEventDestroy(c->ev_samples);
   for (hipEvent_t e : c->prof.pool) (void)hipEventDestroy(e);
   if (c->side) {
     (void)hipStreamSynchronize(c->side);
@@ -676,6 +682,11 @@ int gmcp_ccd_swept(gmcp_ctx *c, const void *xs, const void *xm, const void *dxs,
                                                   (const float *)dxm);
   c->swept_ready = e == hipSuccess;
   return fail(c, e);
+}
+
+int gmcp_wait_samples(gmcp_ctx *c) {
+  if (!c || !c->assembled) return GMCP_E_ARG;
+  return fail(c, hipStreamWaitEvent(c->stream, c->ev_samples, 0));
 }
 
 int gmcp_ccd_finish(gmcp_ctx *c, const void *dxs, const void *dxm, void *alpha) {

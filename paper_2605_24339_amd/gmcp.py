@@ -320,10 +320,11 @@ class Context:
         gradient, BSR Hessian), step bound.  Unchecked and not profiled, the
         step bound's swept part (grid + additive CCD, independent of the
         assembly) runs on a second stream, forked from the current one after
-        the broad phase and joined back before the final bound, so it overlaps
-        the assembly (also inside a captured graph); the broad phase, whose
-        query walks its list with a grid sized to the whole device, runs
-        alone."""
+        the broad phase, so it overlaps the assembly (also inside a captured
+        graph), and the rest of the bound follows on that stream as soon as
+        the narrow phase has written the samples, beside the row kernels; the
+        two streams join at the end.  The broad phase, whose query walks its
+        list with a grid sized to the whole device, runs alone."""
         if check or self._profiling:
             self.broadphase(xs, xm, check=check)
             A = self.assemble(xs, xm, check=check)
@@ -337,8 +338,11 @@ class Context:
         with torch.cuda.stream(self._side):
             self.ccd_swept(xs, xm, dxs, dxm)
         A = self.assemble(xs, xm, check=False)
+        with torch.cuda.stream(self._side):
+            self._bind()
+            _check(N.lib().gmcp_wait_samples(self._ctx), "gmcp_wait_samples")
+            alpha = self.ccd_finish(dxs, dxm)
         main.wait_stream(self._side)
-        alpha = self.ccd_finish(dxs, dxm)
         return A, alpha
 
     def capture(self, xs, xm, dxs, dxm=None) -> "torch.cuda.CUDAGraph":
