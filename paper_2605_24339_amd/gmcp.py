@@ -343,6 +343,7 @@ class Context:
             _check(N.lib().gmcp_wait_samples(self._ctx), "gmcp_wait_samples")
             alpha = self.ccd_finish(dxs, dxm)
         main.wait_stream(self._side)
+        self._bind()  # later calls (``status``) follow the caller's stream again
         return A, alpha
 
     def capture(self, xs, xm, dxs, dxm=None) -> "torch.cuda.CUDAGraph":
