@@ -1143,6 +1143,7 @@ struct RowArgs {
   int64_t cap_nnzb;
   R *grad;   // nullable: written by the writing pass (pass 1) or alone (pass 2)
   int light_bound;  // column insertions of a light row (32, 64, 128 or 256)
+  bool split;       // light and heavy rows in launches of their own
 };
 
 constexpr int kRowWaves = 2;   // light rows
@@ -1150,6 +1151,7 @@ constexpr int kRowWaves = 2;   // light rows
 // held nearly all LDS of the card while the light rows ran beside them (256
 // environments, step: 5.97 ms, with half as many 5.71)
 constexpr int kHeavyWaves = 1;
+constexpr int64_t kSplitRows = 16384;  // rows from which light and heavy ones are launched apart
 // the list-walking row kernels use fixed grids, by default many times the
 // blocks resident at once (kDefaultRowBlocks light, kDefaultHeavyBlocks
 // heavy): a block's share of the list is short, so blocks that start late
@@ -1429,7 +1431,9 @@ constexpr size_t row_lds_wave(int slots, int pass, bool heavy, int light_bound) 
           15) / 16 * 16;
 }
 
-template <typename R, int PASS, bool HEAVY>  // HEAVY: the heavy-row list (large LDS tables), same code
+// HEAVY: the heavy rows (large LDS tables), without a.split all rows, same code;
+// rlist / rcount: the light rows' list, and a.V entries on the heavy rows'
+template <typename R, int PASS, bool HEAVY>
 __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slots, const int4 *__restrict__ rlist,
                                                            const int32_t *__restrict__ rcount) {
   constexpr int pass = PASS;
@@ -1454,7 +1458,7 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
   uint16_t *smap = reinterpret_cast<uint16_t *>(snrm + 3 * kRowSrc);  // place in `dense` of a slot's column
   if (pass == 1 || pass == 3) {
     const int64_t nnzb = a.row_ptr[a.V];
-    if (pass == 1 && !HEAVY && blockIdx.x == 0 && threadIdx.x == 0) {  // the BSR's block count
+    if (pass == 1 && HEAVY != a.split && blockIdx.x == 0 && threadIdx.x == 0) {  // the BSR's block count
       a.st->nnzb = (unsigned long long)nnzb;
       if (nnzb > a.cap_nnzb) atomicCAS(&a.st->code, 0, GMCP_E_CAPACITY);
     }
@@ -1478,8 +1482,11 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
     carry = __builtin_amdgcn_readlane(lo, kWave - 1);
     return lo;
   };
-  // the waves walk the list of rows with contributions (k_row_pre)
-  const int64_t nlist = *rcount;
+  // the waves walk the list of rows with contributions (k_row_pre); without
+  // a split the heavy instance walks the light rows, then the heavy ones
+  const int64_t nl = HEAVY == a.split ? 0 : rcount[0];
+  const int64_t nlist = nl + (HEAVY ? rcount[1] : 0);
+  auto listed = [&](int64_t i) { return i < nl ? rlist[i] : rlist[a.V + i - nl]; };
   const int nw = blockDim.x / kWave;
   // rows in dispatch order: an XCD-by-XCD mapping of the list measured
   // several times slower (the rows with work cluster in the list, so the
@@ -1496,12 +1503,12 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
     if (pass == 3 || r.y + lane >= r.z) return 0;
     return r.x < a.Vs ? a.s_vt[r.y + lane] : a.m_vt[r.y + lane];
   };
-  int4 rr_c = li < nlist ? rlist[li] : make_int4(0, 0, 0, 0);
-  int4 rr_n = li + lstride < nlist ? rlist[li + lstride] : make_int4(0, 0, 0, 0);
+  int4 rr_c = li < nlist ? listed(li) : make_int4(0, 0, 0, 0);
+  int4 rr_n = li + lstride < nlist ? listed(li + lstride) : make_int4(0, 0, 0, 0);
   int ent_c = li < nlist ? first_ent(rr_c) : 0;
   for (; li < nlist; li += lstride) {
     const int ent_n = li + lstride < nlist ? first_ent(rr_n) : 0;
-    const int4 rr_nn = li + 2 * lstride < nlist ? rlist[li + 2 * lstride] : make_int4(0, 0, 0, 0);
+    const int4 rr_nn = li + 2 * lstride < nlist ? listed(li + 2 * lstride) : make_int4(0, 0, 0, 0);
     [&](const int4 rr, const int ent0) {
   wave_sync();  // the previous row's LDS reads are done
   const int64_t row = rr.x;
@@ -2105,6 +2112,7 @@ RowArgs<R> row_args(gmcp_ctx *c, const gmcp_bsr *H) {
   ra.cap_nnzb = H ? H->cap_nnzb : 0;
   ra.grad = nullptr;
   ra.light_bound = light_row_bound(c);
+  ra.split = true;
   return ra;
 }
 
@@ -2208,10 +2216,15 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   RowArgs<R> ra = row_args<R>(c, H);
   ra.grad = grad;
   const int nw = kRowWaves;
-  // light and heavy rows (and the master-triangle sums) are independent:
-  // the heavy ones run on the library's second stream, forked after the row
-  // lists and joined before what reads both (not while profiling)
-  const bool par = c->side != nullptr && !c->prof.on;
+  // Many rows: light and heavy rows are launched apart, and as they (and the
+  // master-triangle sums) are independent the heavy ones run on the library's
+  // second stream, forked after the row lists and joined before what reads
+  // both (not while profiling).  Few rows: one launch on one stream walks both
+  // lists; a fork and its join cost more than a row kernel takes there.
+  // One launch against two (step): 931 rows 195 and 300 us (enqueued one by
+  // one), 9136 rows 173.5 and 186.5, 36893 rows 263 and 249.
+  ra.split = c->V >= kSplitRows;
+  const bool par = ra.split && c->side != nullptr && !c->prof.on;
   const hipStream_t hs = par ? c->side : s;
   auto fork = [&]() {
     if (!par) return hipSuccess;
@@ -2247,14 +2260,13 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   const int64_t rneed = (c->V + nw - 1) / nw;
   const int64_t rmax = light_row_blocks(c);
   const dim3 rgrid((unsigned)(rneed < rmax ? (rneed > 0 ? rneed : 1) : rmax));
-  const dim3 hgrid((unsigned)heavy_row_blocks(c));
-  const int4 *light = b.rlist, *heavy = b.rlist + c->V;
-  const int32_t *nlight = b.rcount, *nheavy = b.rcount + 1;
+  const dim3 hgrid((unsigned)std::max<int64_t>(
+      1, ra.split ? heavy_row_blocks(c) : std::min<int64_t>(heavy_row_blocks(c), c->V)));
   if (grad && !H) {  // gradient alone: the row kernel's gradient-only pass
     prof_mark(c, ST_GRAD, 0);
     if ((e = fork()) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_rows<R, 2, true>), hgrid, dim3(kWave * kHeavyWaves), 0, hs, ra, 64, heavy, nheavy);
-    hipLaunchKernelGGL((k_rows<R, 2, false>), rgrid, dim3(kWave * nw), 0, s, ra, 64, light, nlight);
+    hipLaunchKernelGGL((k_rows<R, 2, true>), hgrid, dim3(kWave * kHeavyWaves), 0, hs, ra, 64, b.rlist, b.rcount);
+    if (ra.split) hipLaunchKernelGGL((k_rows<R, 2, false>), rgrid, dim3(kWave * nw), 0, s, ra, 64, b.rlist, b.rcount);
     if ((e = join()) != hipSuccess) return e;
     prof_mark(c, ST_GRAD, 1);
   }
@@ -2272,14 +2284,15 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     };
     if ((e = fork()) != hipSuccess) return e;
     prof_mark(c, ST_ROWS_COUNT_H, 0);
-    hipLaunchKernelGGL((k_rows<R, 0, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 0, true), hs, ra, hslots, heavy,
-                       nheavy);
+    hipLaunchKernelGGL((k_rows<R, 0, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 0, true), hs, ra, hslots,
+                       b.rlist, b.rcount);
     prof_mark(c, ST_ROWS_COUNT_H, 1);
     if ((e = mark_side()) != hipSuccess) return e;
     if (sums) mtri(hs);  // read by the writing pass, beside the scan
     prof_mark(c, ST_ROWS_COUNT, 0);
-    hipLaunchKernelGGL((k_rows<R, 0, false>), rgrid, dim3(kWave * nw), lds(lslots, 0, false), s, ra, lslots, light,
-                       nlight);
+    if (ra.split)
+      hipLaunchKernelGGL((k_rows<R, 0, false>), rgrid, dim3(kWave * nw), lds(lslots, 0, false), s, ra, lslots, b.rlist,
+                         b.rcount);
     prof_mark(c, ST_ROWS_COUNT, 1);
     if ((e = wait_side()) != hipSuccess) return e;
     e = scan_exclusive(c, b.row_cnt, H->row_ptr, c->V + 1);
@@ -2287,19 +2300,21 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     if ((e = fork()) != hipSuccess) return e;
     if (sums && (e = join()) != hipSuccess) return e;  // the sums
     prof_mark(c, ST_ROWS_FILL_H, 0);
-    hipLaunchKernelGGL((k_rows<R, 1, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 1, true), hs, ra, hslots, heavy,
-                       nheavy);
+    hipLaunchKernelGGL((k_rows<R, 1, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 1, true), hs, ra, hslots,
+                       b.rlist, b.rcount);
     prof_mark(c, ST_ROWS_FILL_H, 1);
     prof_mark(c, ST_ROWS_FILL, 0);
-    hipLaunchKernelGGL((k_rows<R, 1, false>), rgrid, dim3(kWave * nw), lds(lslots, 1, false), s, ra, lslots, light,
-                       nlight);
+    if (ra.split)
+      hipLaunchKernelGGL((k_rows<R, 1, false>), rgrid, dim3(kWave * nw), lds(lslots, 1, false), s, ra, lslots, b.rlist,
+                         b.rcount);
     prof_mark(c, ST_ROWS_FILL, 1);
     if ((e = join()) != hipSuccess) return e;
     if (c->V > c->Vs) {
       prof_mark(c, ST_ROWS_COPY, 0);
       if ((e = fork()) != hipSuccess) return e;
-      hipLaunchKernelGGL((k_rows<R, 3, true>), hgrid, dim3(kWave * kHeavyWaves), 0, hs, ra, hslots, heavy, nheavy);
-      hipLaunchKernelGGL((k_rows<R, 3, false>), rgrid, dim3(kWave * nw), 0, s, ra, lslots, light, nlight);
+      hipLaunchKernelGGL((k_rows<R, 3, true>), hgrid, dim3(kWave * kHeavyWaves), 0, hs, ra, hslots, b.rlist, b.rcount);
+      if (ra.split)
+        hipLaunchKernelGGL((k_rows<R, 3, false>), rgrid, dim3(kWave * nw), 0, s, ra, lslots, b.rlist, b.rcount);
       if ((e = join()) != hipSuccess) return e;
       prof_mark(c, ST_ROWS_COPY, 1);
     }
