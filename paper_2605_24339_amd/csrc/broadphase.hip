@@ -243,7 +243,13 @@ __global__ __launch_bounds__(kThreads) void k_master_boxes(const R *__restrict__
 }
 
 // place the master ids in their cells after the count and its scan (the
-// counters return to zero); same cell ranges as the count
+// counters return to zero); same cell ranges as the count.  L lanes per
+// triangle take its cells in turn: one where there are many triangles, 16
+// where few would leave most of the card idle with one long chain of atomics
+// each (1280 triangles of some 100 cells: 23.4 us with one lane).
+constexpr int kInsertLanes = 16;
+constexpr int64_t kInsertWide = 16384;  // triangles up to which 16 lanes fit the card at once
+template <int L>
 __global__ __launch_bounds__(kThreads) void k_grid_insert(const float4 *__restrict__ mbox,
                                                            const int32_t *__restrict__ m_env,
                                                            const EnvInfo *__restrict__ env,
@@ -252,12 +258,13 @@ __global__ __launch_bounds__(kThreads) void k_grid_insert(const float4 *__restri
                                                            const int32_t *__restrict__ cell_start,
                                                            int32_t *__restrict__ items, int64_t cap_items,
                                                            int64_t total_cells, DevStatus *st) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, t = i / L;
+  const int sub = (int)(i % L);
   if (t >= Tm) return;
   // the overflow is reported by thread 0 whatever its own triangle does
   const int64_t total = cell_start[total_cells];
   const bool fits = total <= cap_items;
-  if (!fits && t == 0) {
+  if (!fits && i == 0) {
     atomicMax(&st->need_items, (unsigned long long)total);
     atomicCAS(&st->code, 0, GMCP_E_CAPACITY);
   }
@@ -273,19 +280,26 @@ __global__ __launch_bounds__(kThreads) void k_grid_insert(const float4 *__restri
     c1[d] = cell_coord(g, hi[d], d);
   }
   const int64_t base = env[e].cell0;
-  // the box's cells four at a time: their atomics in flight together (the
-  // cell coordinates stepped x-fastest, no divisions)
-  const int nxy = (c1[0] - c0[0] + 1) * (c1[1] - c0[1] + 1);
-  const int ncell = nxy * (c1[2] - c0[2] + 1);
+  // the lane's cells four at a time: their atomics in flight together (the
+  // cell coordinates stepped x-fastest, no divisions but the lane's first)
+  const int nx = c1[0] - c0[0] + 1, ny = c1[1] - c0[1] + 1;
+  const int nall = nx * ny * (c1[2] - c0[2] + 1);
+  const int ncell = (nall - sub + L - 1) / L;  // cells sub, sub + L, ...
   int x = c0[0], y = c0[1], z = c0[2];
+  if (L > 1) {
+    x += sub % nx;
+    y += sub / nx % ny;
+    z += sub / nx / ny;
+  }
   for (int i0 = 0; i0 < ncell; i0 += 4) {
     int64_t cell[4];
     int slot[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       cell[k] = base + ((int64_t)z * g.ny + y) * g.nx + x;
-      if (++x > c1[0]) {
-        x = c0[0];
+      x += L;
+      while (x > c1[0]) {
+        x -= nx;
         if (++y > c1[1]) {
           y = c0[1];
           ++z;
@@ -767,8 +781,11 @@ hipError_t build_grid(gmcp_ctx *c, const R *xs, const R *xm, const R *dxs, const
                        c->Tm, mbox, b.m_env, b.env, box, grid, c->n_env, swept ? 1 : 0, cnt);
   hipError_t e = scan_exclusive(c, cnt, start, c->total_cells + 1, swept, grid);
   if (e != hipSuccess) return e;
-  if (c->Tm)
-    hipLaunchKernelGGL(k_grid_insert, dim3(nblk(c->Tm)), dim3(kThreads), 0, s, mbox, b.m_env, b.env, grid, c->Tm,
+  if (c->Tm && c->Tm <= kInsertWide)
+    hipLaunchKernelGGL(k_grid_insert<kInsertLanes>, dim3(nblk(kInsertLanes * c->Tm)), dim3(kThreads), 0, s, mbox,
+                       b.m_env, b.env, grid, c->Tm, cnt, start, items, c->caps.grid_items, c->total_cells, b.status);
+  else if (c->Tm)
+    hipLaunchKernelGGL(k_grid_insert<1>, dim3(nblk(c->Tm)), dim3(kThreads), 0, s, mbox, b.m_env, b.env, grid, c->Tm,
                        cnt, start, items, c->caps.grid_items, c->total_cells, b.status);
   return hipGetLastError();
 }
