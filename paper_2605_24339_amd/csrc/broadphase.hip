@@ -790,6 +790,34 @@ hipError_t build_grid(gmcp_ctx *c, const R *xs, const R *xm, const R *dxs, const
   return hipGetLastError();
 }
 
+// One block: the status word and the candidate total (the query blocks'
+// counts: no single-address atomics in the query) into pinned host memory,
+// then the sticky error cleared.  One launch and one wait; as two copies with
+// a wait each and a third to clear, a status call took 50 us, three of them a
+// fifth of a float64 Newton iteration's sequence.
+__global__ __launch_bounds__(1024) void k_status(DevStatus *st, const int32_t *__restrict__ blk, int n,
+                                                 StatusHost *out) {
+  __shared__ long long part[1024 / kWave];
+  long long s = 0;
+  for (int i = threadIdx.x; i < n; i += 1024) s += blk[i];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
+  if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = s;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int k = 1; k < 1024 / kWave; ++k) s += part[k];
+  out->st = *st;
+  out->n_cand = s;
+  st->code = 0;
+  st->index = ~0ull;
+  st->need_items = st->need_cand = st->need_active = st->need_pairs = st->need_row = 0;
+}
+
+hipError_t launch_status(gmcp_ctx *c) {
+  hipLaunchKernelGGL(k_status, dim3(1), dim3(1024), 0, c->stream, c->b.status, c->b.cand_blk, (int)c->query_blocks,
+                     c->status_host);
+  return hipGetLastError();
+}
+
 template <typename R>
 hipError_t launch_broadphase(gmcp_ctx *c, const R *xs, const R *xm) {
   Buffers &b = c->b;

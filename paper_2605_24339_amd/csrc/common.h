@@ -34,6 +34,11 @@ struct DevStatus {
   unsigned long long mortar_alloc;  // clipped samples: pairs << 32 | records, one atomic per triangle
 };
 
+struct StatusHost {  // in pinned host memory: a status call's answer
+  DevStatus st;
+  long long n_cand;
+};
+
 // --------------------------------------------------------- per environment
 struct EnvInfo {
   double kappa, dhat, delta_T, cell;
@@ -174,6 +179,7 @@ struct gmcp_ctx {
   // graph capture); null if creation failed (then everything runs in order)
   hipStream_t side;
   hipEvent_t ev_fork, ev_join;
+  gmcp::StatusHost *status_host;
   hipEvent_t ev_samples;  // the last assembly's sample records are written
   bool f64, kinematic, mortar, features;
   int n_env;
@@ -222,6 +228,7 @@ inline int heavy_row_blocks(const gmcp_ctx *c) {
 
 // ------------------------------------------------------------ launchers
 // each returns hipSuccess or the launch error
+hipError_t launch_status(gmcp_ctx *c);  // status word to c->status_host, then its error cleared
 // side = true uses the second scratch (the swept grid's scans may run on
 // another stream, concurrently with the broad phase and assembly)
 // grid: the environments' grids of a cell-count scan (only their used cells

@@ -518,8 +518,10 @@ int gmcp_create(gmcp_ctx **out, const gmcp_layout *L, const gmcp_caps *caps, con
   } else {
     c->side = nullptr;
   }
-  if (hipEventCreateWithFlags(&c->ev_samples, hipEventDisableTiming) != hipSuccess) {
-    c->ev_samples = nullptr;
+  c->ev_samples = nullptr;
+  c->status_host = nullptr;
+  if (hipEventCreateWithFlags(&c->ev_samples, hipEventDisableTiming) != hipSuccess ||
+      hipHostMalloc((void **)&c->status_host, sizeof(gmcp::StatusHost), hipHostMallocDefault) != hipSuccess) {
     gmcp_destroy(c);
     return GMCP_E_HIP;
   }
@@ -530,6 +532,12 @@ int gmcp_create(gmcp_ctx **out, const gmcp_layout *L, const gmcp_caps *caps, con
 void gmcp_destroy(gmcp_ctx *c) {
   if (!c) return;
   if (c->ev_samples) (void)hipEventDestroy(c->ev_samples);
+  if (c->status_host) {  // also while another stream of this thread is captured
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    (void)hipHostFree(c->status_host);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
   for (hipEvent_t e : c->prof.pool) (void)hipEventDestroy(e);
   if (c->side) {
     (void)hipStreamSynchronize(c->side);
@@ -741,26 +749,15 @@ int gmcp_candidates(gmcp_ctx *c, int32_t *cand_off, int32_t *cand, int64_t cap) 
 
 int gmcp_status(gmcp_ctx *c, gmcp_status_info *info) {
   if (!c || !info) return GMCP_E_ARG;
-  DevStatus st;
-  if (hipMemcpyAsync(&st, c->b.status, sizeof(st), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
-      hipStreamSynchronize(c->stream) != hipSuccess)
-    return GMCP_E_HIP;
+  if (gmcp::launch_status(c) != hipSuccess || hipStreamSynchronize(c->stream) != hipSuccess) return GMCP_E_HIP;
+  const DevStatus &st = c->status_host->st;
+  const int64_t ncand = c->status_host->n_cand;
   memset(info, 0, sizeof(*info));
   info->code = st.code;
   info->index = st.index == ~0ull ? -1 : (int64_t)st.index;
   info->n_active = (int64_t)st.n_active;
   info->n_pairs = (int64_t)st.n_pairs;
   info->nnzb = (int64_t)st.nnzb;
-  // candidates: the query blocks' totals (no single-address atomics in the query)
-  int64_t ncand = 0;
-  if (c->query_blocks > 0) {
-    std::vector<int32_t> blk(c->query_blocks);
-    if (hipMemcpyAsync(blk.data(), c->b.cand_blk, sizeof(int32_t) * blk.size(), hipMemcpyDeviceToHost, c->stream) !=
-            hipSuccess ||
-        hipStreamSynchronize(c->stream) != hipSuccess)
-      return GMCP_E_HIP;
-    for (int32_t v : blk) ncand += v;
-  }
   info->n_candidates = ncand;
   info->n_swept = (int64_t)st.n_swept;
   info->need.grid_cells = c->caps.grid_cells;
@@ -770,12 +767,6 @@ int gmcp_status(gmcp_ctx *c, gmcp_status_info *info) {
   info->need.active = (int64_t)st.n_active;
   info->need.pairs = (int64_t)st.n_pairs;
   info->need.row_entries = (int64_t)st.need_row;
-  // clear the sticky error
-  DevStatus clr = st;
-  clr.code = 0;
-  clr.index = ~0ull;
-  clr.need_items = clr.need_cand = clr.need_active = clr.need_pairs = clr.need_row = 0;
-  if (hipMemcpy(c->b.status, &clr, sizeof(clr), hipMemcpyHostToDevice) != hipSuccess) return GMCP_E_HIP;
   return GMCP_OK;
 }
 
