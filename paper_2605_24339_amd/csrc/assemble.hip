@@ -1193,6 +1193,25 @@ __device__ inline int row_rank(const int32_t *dense, int n4, int32_t c) {
   return r;
 }
 
+// sum over the four lanes of an aligned group, by lane moves in the vector unit
+template <typename R>
+__device__ inline R quad_lane(R v, bool far) {
+  int w[sizeof(R) / 4];
+  __builtin_memcpy(w, &v, sizeof(R));
+#pragma unroll
+  for (int k = 0; k < (int)(sizeof(R) / 4); ++k)
+    w[k] = far ? __builtin_amdgcn_mov_dpp(w[k], 0x4E, 0xF, 0xF, true)   // quad_perm [2, 3, 0, 1]
+               : __builtin_amdgcn_mov_dpp(w[k], 0xB1, 0xF, 0xF, true);  // quad_perm [1, 0, 3, 2]
+  __builtin_memcpy(&v, w, sizeof(R));
+  return v;
+}
+template <typename R>
+__device__ inline R quad_sum(R v) {
+  v += quad_lane(v, false);
+  v += quad_lane(v, true);
+  return v;
+}
+
 // Four lanes per master triangle with contact pairs: the sum over its pairs
 // (bucket order: sorted by slave triangle) of the master-master sums times
 // n_T n_T^T - six vertex pairs (00 01 02 11 12 22) of six symmetric entries -
@@ -1242,14 +1261,8 @@ __global__ __launch_bounds__(kThreads) void k_mtri(const Pair<R> *__restrict__ p
       }
     }
   }
-  for (int z = 0; z < 36; ++z) {
-    h[z] += __shfl_xor(h[z], 1, kWave);
-    h[z] += __shfl_xor(h[z], 2, kWave);
-  }
-  for (int z = 0; z < 9; ++z) {
-    g[z] += __shfl_xor(g[z], 1, kWave);
-    g[z] += __shfl_xor(g[z], 2, kWave);
-  }
+  for (int z = 0; z < 36; ++z) h[z] = quad_sum(h[z]);
+  for (int z = 0; z < 9; ++z) g[z] = quad_sum(g[z]);
   if (b == e || sub != 0) return;
   R *out = mtri + 45 * t;
   for (int z = 0; z < 36; ++z) out[z] = h[z];
@@ -1920,35 +1933,87 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
 }
 
 
-// gradient row by row: slave a: sum_T -gs[T][a] n_T; master j: sum over
-// the pairs of its master triangles (sorted by slave triangle) gm[j] n_T
-// MODE 0: gradient (tri_sum gs, Pair::gm); MODE 1: HVP (hv_tri, hv_pair)
-template <typename R, int MODE>
-__global__ __launch_bounds__(kThreads) void k_grad(RowArgs<R> a, const R *__restrict__ hv_tri,
-                                                    const R *__restrict__ hv_pair, R *__restrict__ out) {
-  int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Four lanes per master triangle with contact pairs: the Hessian-vector sums
+// hv_pair n_T of its three vertices, over its pairs in bucket order (lane s
+// takes the pairs s, s + 4, ..., a fixed butterfly), into the gradient slots
+// of k_mtri's record (read by the assembly's own row kernels only)
+template <typename R>
+__global__ __launch_bounds__(kThreads) void k_hvp_mtri(RowArgs<R> a, const R *__restrict__ hv_pair, int64_t Tm,
+                                                        R *__restrict__ mtri) {
+  const int64_t gt = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t t = gt >> 2;
+  const int sub = (int)(gt & 3);
+  const bool live = t < Tm && (int64_t)a.st_r->n_pairs <= a.cap_pairs;
+  const int b = live ? a.mp_off[t] : 0, e = live ? a.mp_off[t + 1] : 0;
+  if (__all(b == e)) return;  // wave-uniform: the groups below exchange lanes
+  R g[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  for (int i0 = b + sub; i0 < e; i0 += 16) {
+    R h[4][3], nn[4][3];
+    int p[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) p[k] = i0 + 4 * k < e ? a.mp_list[i0 + 4 * k] : -1;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (p[k] < 0) continue;
+      const int64_t T = a.pair[p[k]].T;
+      for (int m = 0; m < 3; ++m) h[k][m] = hv_pair[3 * (int64_t)p[k] + m];
+      for (int d = 0; d < 3; ++d) nn[k][d] = a.tri_nrm[3 * T + d];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (p[k] < 0) continue;
+      for (int m = 0; m < 3; ++m)
+        for (int d = 0; d < 3; ++d) g[3 * m + d] += h[k][m] * nn[k][d];
+    }
+  }
+  for (int z = 0; z < 9; ++z) g[z] = quad_sum(g[z]);
+  if (b == e || sub != 0) return;
+  for (int z = 0; z < 9; ++z) mtri[45 * t + 36 + z] = g[z];
+}
+
+// Hessian-vector product row by row: slave a: sum_T -hv_tri[T][a] n_T; master
+// j: the sums of its triangles (k_hvp_mtri).  Thread per row, four incident
+// triangles at a time with their loads in flight together, added in adjacency
+// order.  (Walking the master triangles' pairs from every row, one dependent
+// load after the other, took 61 us under one large indentation.)
+template <typename R>
+__global__ __launch_bounds__(kThreads) void k_hvp_rows(RowArgs<R> a, const R *__restrict__ hv_tri,
+                                                        R *__restrict__ out) {
+  const int64_t row = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (row >= a.V) return;
   R g[3] = {0, 0, 0};
   if ((int64_t)a.st_r->n_pairs <= a.cap_pairs) {
-    if (row < a.Vs) {
-      for (int s = a.s_vt_off[row]; s < a.s_vt_off[row + 1]; ++s) {
-        int ent = a.s_vt[s], t = ent >> 2, corner = ent & 3;
-        if (a.tri_npair[t] == 0) continue;
-        R cf = -(MODE == 0 ? a.tri_sum[9 * (int64_t)t + 6 + corner] : hv_tri[3 * (int64_t)t + corner]);
-        const R *nn = a.tri_nrm + 3 * (int64_t)t;
-        for (int d = 0; d < 3; ++d) g[d] += cf * nn[d];
+    const bool slave = row < a.Vs;
+    const int64_t vid = slave ? row : row - a.Vs;
+    const int sb = slave ? a.s_vt_off[vid] : a.m_vt_off[vid];
+    const int se = slave ? a.s_vt_off[vid + 1] : a.m_vt_off[vid + 1];
+    const int32_t *vt = slave ? a.s_vt : a.m_vt;
+    for (int s0 = sb; s0 < se; s0 += 4) {
+      int t[4], corner[4], np[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int ent = s0 + k < se ? vt[s0 + k] : -4;
+        t[k] = ent >> 2;
+        corner[k] = ent & 3;
       }
-    } else {
-      int64_t vid = row - a.Vs;
-      for (int s = a.m_vt_off[vid]; s < a.m_vt_off[vid + 1]; ++s) {
-        int ent = a.m_vt[s], t = ent >> 2, corner = ent & 3;
-        for (int i = a.mp_off[t]; i < a.mp_off[t + 1]; ++i) {
-          int p = a.mp_list[i];
-          R cf = MODE == 0 ? a.pair[p].gm[corner] : hv_pair[3 * (int64_t)p + corner];
-          const R *nn = a.tri_nrm + 3 * (int64_t)a.pair[p].T;
-          for (int d = 0; d < 3; ++d) g[d] += cf * nn[d];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        np[k] = t[k] < 0 ? 0 : (slave ? a.tri_npair[t[k]] : a.mp_off[t[k] + 1] - a.mp_off[t[k]]);
+      R c[4][3];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (np[k] <= 0) continue;
+        if (slave) {
+          const R cf = -hv_tri[3 * (int64_t)t[k] + corner[k]];
+          for (int d = 0; d < 3; ++d) c[k][d] = cf * a.tri_nrm[3 * (int64_t)t[k] + d];
+        } else {
+          for (int d = 0; d < 3; ++d) c[k][d] = a.mtri[45 * (int64_t)t[k] + 36 + 3 * corner[k] + d];
         }
       }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (np[k] > 0)
+          for (int d = 0; d < 3; ++d) g[d] += c[k][d];
     }
   }
   for (int d = 0; d < 3; ++d) out[3 * row + d] = g[d];
@@ -1990,6 +2055,21 @@ __global__ void k_fill_r(R *p, R v, int64_t n) {
   for (; i < n; i += stride) p[i] = v;
 }
 
+// every sample's outputs (each nullable) as an inactive sample's, in one
+// launch: six fills took 2 to 3 us each
+template <typename R>
+__global__ __launch_bounds__(kThreads) void k_fill_samples(int32_t *M, R *g, R *bm, R *c1, R *c2, R *p, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
+    if (M) M[i] = -1;
+    if (g) g[i] = R(0);
+    if (bm)
+      for (int64_t d = 0; d < 3; ++d) bm[d * n + i] = R(0);
+    if (c1) c1[i] = R(0);
+    if (c2) c2[i] = R(0);
+    if (p) p[i] = R(0);
+  }
+}
+
 template <typename R>
 __global__ void k_export(const Rec<R> *__restrict__ rec, const DevStatus *st, int64_t cap_active, int32_t *M,
                          R *g, R *bm, R *c1, R *c2, R *p) {
@@ -2022,9 +2102,15 @@ __global__ void k_pair_export(const Pair<R> *__restrict__ pair, const DevStatus 
 }
 
 // HVP, step 1: per slave triangle, s_k = c2 (grad g_k . v_x + v_d[k]);
-// out_d[k] = s_k; triangle sums s_k bs_a; pair sums s_k bm_j
+// out_d[k] = s_k; triangle sums s_k bs_a; pair sums s_k bm_j.
+// 16 lanes per slave triangle with records: a lane takes a record (its
+// product with vx and the sample's vd, the triangle's sums by a fixed
+// butterfly), then a pair, whose records it adds in order from LDS.  What
+// bounds it is one triangle's chain of loads: a thread per triangle walking
+// its records once per pair took 81 us under one large indentation.
+constexpr int kHvpLanes = 16;
 template <typename R>
-__global__ void k_hvp_tri(const Rec<R> *__restrict__ rec, const int32_t *__restrict__ tri_roff,
+__global__ __launch_bounds__(kThreads) void k_hvp_tri(const Rec<R> *__restrict__ rec, const int32_t *__restrict__ tri_roff,
                           const int32_t *__restrict__ tri_rcnt, const int32_t *__restrict__ tri_npair,
                           const int32_t *__restrict__ tri_poff, const Pair<R> *__restrict__ pair,
                           const R *__restrict__ tri_nrm, const int32_t *__restrict__ ts,
@@ -2033,49 +2119,71 @@ __global__ void k_hvp_tri(const Rec<R> *__restrict__ rec, const int32_t *__restr
                           bool kinematic, const R *__restrict__ vx, const R *__restrict__ vd, R *__restrict__ od,
                           R *__restrict__ hv_tri, R *__restrict__ hv_pair, const DevStatus *st, int64_t cap_active,
                           int64_t cap_pairs) {
-  int64_t T = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  constexpr int G = kHvpLanes;
+  __shared__ R sh[kThreads][4];  // s, bm of a record
+  __shared__ int32_t shM[kThreads];
+  const int64_t gt = (int64_t)blockIdx.x * kThreads + threadIdx.x, T = gt / G;
+  const int sub = (int)(threadIdx.x % G), grp = (int)threadIdx.x - sub;
   if (T >= Ts) return;
   if ((int64_t)st->n_active > cap_active || (int64_t)st->n_pairs > cap_pairs) return;
-  int rc = tri_rcnt[T];
+  const int rc = tri_rcnt[T];
   if (rc == 0) return;
-  int rb = tri_roff[T];
-  const R *nn = tri_nrm + 3 * T;
-  R vs[3];
+  const int rb = tri_roff[T], pb = tri_poff[T], np = tri_npair[T];
+  R nn[3], vs[3];
+  for (int d = 0; d < 3; ++d) nn[d] = tri_nrm[3 * T + d];
   for (int a = 0; a < 3; ++a) {
     const R *v = vx + 3 * (int64_t)ts[3 * T + a];
     vs[a] = nn[0] * v[0] + nn[1] * v[1] + nn[2] * v[2];
   }
   R ht[3] = {0, 0, 0};
-  int pb = tri_poff[T], np = tri_npair[T];
-  for (int p = pb; p < pb + np; ++p) {
-    const Pair<R> &P = pair[p];
-    R vm[3];
-    for (int m = 0; m < 3; ++m) {
-      if (kinematic) {
-        vm[m] = 0;
-        continue;
-      }
-      const R *v = vx + 3 * (Vs + tm[3 * (int64_t)P.M + m]);
-      vm[m] = nn[0] * v[0] + nn[1] * v[1] + nn[2] * v[2];
-    }
+  for (int p0 = 0; p0 < np; p0 += G) {  // one turn but for a clipped sample's long pair list
+    const int j = p0 + sub;
+    const int32_t Mj = j < np ? pair[pb + j].M : -1;
     R hp[3] = {0, 0, 0};
-    for (int i = rb; i < rb + rc; ++i) {
-      const Rec<R> &r = rec[i];
-      if (r.M != P.M) continue;
-      R bs[3] = {R(1) - r.s1 - r.s2, r.s1, r.s2};
-      R bm[3] = {r.b0, r.b1, r.b2};
-      R dot = -(bs[0] * vs[0] + bs[1] * vs[1] + bs[2] * vs[2]) + bm[0] * vm[0] + bm[1] * vm[1] + bm[2] * vm[2];
-      if (vd) dot += vd[r.k];
-      R s = r.c2 * dot;
-      if (od) od[r.k] = s;
-      for (int q = 0; q < 3; ++q) {
-        ht[q] += s * bs[q];
-        hp[q] += s * bm[q];
+    for (int i0 = 0; i0 < rc; i0 += G) {
+      const int i = i0 + sub;
+      R s = 0, bm[3] = {0, 0, 0};
+      int32_t M = -2;
+      if (i < rc) {
+        const Rec<R> &r = rec[rb + i];
+        M = r.M;
+        const R bs[3] = {R(1) - r.s1 - r.s2, r.s1, r.s2};
+        bm[0] = r.b0;
+        bm[1] = r.b1;
+        bm[2] = r.b2;
+        R vm[3] = {0, 0, 0};
+        if (!kinematic)
+          for (int m = 0; m < 3; ++m) {
+            const R *v = vx + 3 * (Vs + tm[3 * (int64_t)M + m]);
+            vm[m] = nn[0] * v[0] + nn[1] * v[1] + nn[2] * v[2];
+          }
+        R dot = -(bs[0] * vs[0] + bs[1] * vs[1] + bs[2] * vs[2]) + bm[0] * vm[0] + bm[1] * vm[1] + bm[2] * vm[2];
+        if (vd) dot += vd[r.k];
+        s = r.c2 * dot;
+        if (p0 == 0) {
+          if (od) od[r.k] = s;
+          for (int q = 0; q < 3; ++q) ht[q] += s * bs[q];
+        }
+      }
+      wave_sync();  // the previous turn's reads are done
+      shM[threadIdx.x] = M;
+      sh[threadIdx.x][0] = s;
+      for (int q = 0; q < 3; ++q) sh[threadIdx.x][1 + q] = bm[q];
+      wave_sync();
+      const int n = rc - i0 < G ? rc - i0 : G;
+      for (int q = 0; q < n; ++q) {
+        if (shM[grp + q] != Mj) continue;
+        const R sq = sh[grp + q][0];
+        for (int d = 0; d < 3; ++d) hp[d] += sq * sh[grp + q][1 + d];
       }
     }
-    for (int q = 0; q < 3; ++q) hv_pair[3 * (int64_t)p + q] = hp[q];
+    if (j < np)
+      for (int q = 0; q < 3; ++q) hv_pair[3 * (int64_t)(pb + j) + q] = hp[q];
   }
-  for (int q = 0; q < 3; ++q) hv_tri[3 * T + q] = ht[q];
+  for (int q = 0; q < 3; ++q) {
+    for (int o = G / 2; o > 0; o >>= 1) ht[q] += __shfl_xor(ht[q], o, kWave);
+    if (sub == 0) hv_tri[3 * T + q] = ht[q];
+  }
 }
 
 inline unsigned nblk(int64_t n, int t = kThreads) { return (unsigned)((n + t - 1) / t); }
@@ -2330,13 +2438,15 @@ hipError_t launch_hvp(gmcp_ctx *c, const R *vx, const R *vd, R *ox, R *od) {
   if (od) hipLaunchKernelGGL(k_fill_r<R>, dim3(nblk(c->Ns) > 4096 ? 4096 : nblk(c->Ns)), dim3(kThreads), 0, s, od,
                              R(0), c->Ns);
   if (c->Ts)
-    hipLaunchKernelGGL(k_hvp_tri<R>, dim3(nblk(c->Ts)), dim3(kThreads), 0, s, (const Rec<R> *)b.rec, b.tri_roff,
+    hipLaunchKernelGGL(k_hvp_tri<R>, dim3(nblk(kHvpLanes * c->Ts)), dim3(kThreads), 0, s, (const Rec<R> *)b.rec, b.tri_roff,
                        b.tri_rcnt, b.tri_npair, b.tri_poff, (const Pair<R> *)b.pair, (const R *)b.tri_nrm, c->ts,
                        c->tm, b.s_env, b.env, b.rule, c->Ts, c->Vs, c->kinematic, vx, vd, od, (R *)b.hv_tri,
                        (R *)b.hv_pair, b.status, c->caps.active, c->caps.pairs);
   RowArgs<R> ra = row_args<R>(c, nullptr);
-  hipLaunchKernelGGL((k_grad<R, 1>), dim3(nblk(c->V)), dim3(kThreads), 0, s, ra, (const R *)b.hv_tri,
-                     (const R *)b.hv_pair, ox);
+  if (!c->kinematic && c->Tm)
+    hipLaunchKernelGGL(k_hvp_mtri<R>, dim3(nblk(4 * c->Tm)), dim3(kThreads), 0, s, ra, (const R *)b.hv_pair, c->Tm,
+                       (R *)b.mtri);
+  hipLaunchKernelGGL(k_hvp_rows<R>, dim3(nblk(c->V)), dim3(kThreads), 0, s, ra, (const R *)b.hv_tri, ox);
   return hipGetLastError();
 }
 
@@ -2345,12 +2455,7 @@ hipError_t launch_sample_results(gmcp_ctx *c, int32_t *M, R *g, R *bm, R *c1, R 
   hipStream_t s = c->stream;
   unsigned nb = nblk(c->Ns) > 4096 ? 4096 : nblk(c->Ns);
   if (!c->Ns) return hipSuccess;
-  if (M && fill_i32(c, M, -1, c->Ns) != hipSuccess) return hipGetLastError();
-  if (g) hipLaunchKernelGGL(k_fill_r<R>, dim3(nb), dim3(kThreads), 0, s, g, R(0), c->Ns);
-  if (bm) hipLaunchKernelGGL(k_fill_r<R>, dim3(nb), dim3(kThreads), 0, s, bm, R(0), 3 * c->Ns);
-  if (c1) hipLaunchKernelGGL(k_fill_r<R>, dim3(nb), dim3(kThreads), 0, s, c1, R(0), c->Ns);
-  if (c2) hipLaunchKernelGGL(k_fill_r<R>, dim3(nb), dim3(kThreads), 0, s, c2, R(0), c->Ns);
-  if (p) hipLaunchKernelGGL(k_fill_r<R>, dim3(nb), dim3(kThreads), 0, s, p, R(0), c->Ns);
+  hipLaunchKernelGGL(k_fill_samples<R>, dim3(nb), dim3(kThreads), 0, s, M, g, bm, c1, c2, p, c->Ns);
   hipLaunchKernelGGL(k_export<R>, dim3(nblk(c->caps.active)), dim3(kThreads), 0, s, (const Rec<R> *)c->b.rec,
                      c->b.status, c->caps.active, M, g, bm, c1, c2, p);
   return hipGetLastError();
