@@ -29,6 +29,7 @@ class _Force(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x_s, x_m, delta, scale, backend, g_s, g_m, c1):
         ctx.backend = backend
+        ctx.set_materialize_grads(False)
         ctx.save_for_backward(scale, g_s, g_m, c1)
         return scale * g_s, scale * g_m, scale * c1
 
@@ -36,17 +37,27 @@ class _Force(torch.autograd.Function):
     def backward(ctx, go_s, go_m, go_d):
         scale, g_s, g_m, c1 = ctx.saved_tensors
         be = ctx.backend
+        # each launch costs more than its work on a large pressure map: only
+        # what is asked for is computed (a loss on the pressures has no
+        # gradient in the force outputs, nor one asked in the scale)
+        need_s, need_m, need_d, need_scale = ctx.needs_input_grad[:4]
         z = lambda t, like: torch.zeros_like(like) if t is None else t
-        go_s, go_m, go_d = z(go_s, g_s), z(go_m, g_m), z(go_d, c1)
+        d_scale = None
+        if need_scale:
+            d_scale = ((z(go_s, g_s) * g_s).sum() + (z(go_m, g_m) * g_m).sum() + (z(go_d, c1) * c1).sum())
+            d_scale = d_scale.reshape(scale.shape)
         if be.kinematic:
-            vx = go_s.contiguous()
+            vx = z(go_s, g_s).contiguous()
+        elif go_s is None and go_m is None:
+            vx = g_s.new_zeros(be.Vs + be.Vm, 3)
         else:
-            vx = torch.cat([go_s, go_m], 0).contiguous()
-        hx, hd = be.hvp(vx, go_d.contiguous())
-        d_scale = (go_s * g_s).sum() + (go_m * g_m).sum() + (go_d * c1).sum()
-        h_s = hx[:be.Vs]
-        h_m = torch.zeros_like(g_m) if be.kinematic else hx[be.Vs:]
-        return scale * h_s, scale * h_m, scale * hd, d_scale.reshape(scale.shape), None, None, None, None
+            vx = torch.cat([z(go_s, g_s), z(go_m, g_m)], 0).contiguous()
+        hx, hd = be.hvp(vx, z(go_d, c1).contiguous())
+        d_s = scale * hx[:be.Vs] if need_s else None
+        d_m = None
+        if need_m:
+            d_m = scale * (torch.zeros_like(g_m) if be.kinematic else hx[be.Vs:])
+        return d_s, d_m, scale * hd if need_d else None, d_scale, None, None, None, None
 
 
 class _Energy(torch.autograd.Function):
@@ -60,7 +71,7 @@ class _Energy(torch.autograd.Function):
         g_s = g[:backend.Vs]
         g_m = torch.zeros_like(x_m) if backend.kinematic else g[backend.Vs:]
         ctx.save_for_backward(x_s, x_m, delta, g_s, g_m, S["c1"].clone())
-        return A.energy.sum().clone()
+        return A.energy.sum()
 
     @staticmethod
     def backward(ctx, gE):

@@ -1289,18 +1289,18 @@ __device__ inline void env_energy(const EnergyArgs<R> &a, int e) {
   const uint32_t now = a.tile_act ? *a.epoch : 0;
   constexpr int kV = 1024 / NT;
   double s[kV] = {};
-  for (int tb = t0 + threadIdx.x; tb < t1; tb += 2 * 1024) {
-    // up to 2 kV tiles of the thread, their loads in flight together
-    uint32_t act[2 * kV];
-    double E[2 * kV];
+  constexpr int kN = 8;  // tiles of a thread with their loads in flight together
+  for (int tb = t0 + threadIdx.x; tb < t1; tb += kN * NT) {
+    uint32_t act[kN];
+    double E[kN];
 #pragma unroll
-    for (int v = 0; v < 2 * kV; ++v) {
+    for (int v = 0; v < kN; ++v) {
       const int t = min(tb + v * NT, t1 - 1);
       act[v] = a.tile_act ? a.tile_act[t] : now;
       E[v] = a.tile_E[t];
     }
 #pragma unroll
-    for (int v = 0; v < 2 * kV; ++v)
+    for (int v = 0; v < kN; ++v)
       if (tb + v * NT < t1 && act[v] == now) s[v % kV] += E[v];
   }
 #pragma unroll
@@ -1325,15 +1325,16 @@ __device__ inline void env_energy(const EnergyArgs<R> &a, int e) {
 // pair records overflowed.  A light row has at most a.light_bound column
 // insertions (a power of two); its column table has 2 a.light_bound slots
 // and the hash tables inside it grow in powers of two up to that size.
+constexpr int kPreThreads = 512;  // (with 256 the energies of one large environment outlast the rows)
 template <typename R>
-__global__ __launch_bounds__(kThreads) void k_row_pre(RowArgs<R> a, int4 *__restrict__ rlist,
+__global__ __launch_bounds__(kPreThreads) void k_row_pre(RowArgs<R> a, int4 *__restrict__ rlist,
                                                        int32_t *__restrict__ rcount, int zero_cnt,
                                                        EnergyArgs<R> en, int row_blocks) {
   if ((int)blockIdx.x >= row_blocks) {
-    env_energy<R, kThreads>(en, blockIdx.x - row_blocks);
+    env_energy<R, kPreThreads>(en, blockIdx.x - row_blocks);
     return;
   }
-  const int64_t row = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t row = (int64_t)blockIdx.x * kPreThreads + threadIdx.x;
   const int lane = threadIdx.x & (kWave - 1);
   int n_ent = 0, sb = 0, se = 0;
   if (row < a.V) {
@@ -1363,7 +1364,7 @@ __global__ __launch_bounds__(kThreads) void k_row_pre(RowArgs<R> a, int4 *__rest
     }
   }
   // list appends: wave ballots, block prefix in LDS, one atomic per block and list
-  __shared__ int wl[kThreads / kWave], wh[kThreads / kWave], bl, bh;
+  __shared__ int wl[kPreThreads / kWave], wh[kPreThreads / kWave], bl, bh;
   const int w = threadIdx.x / kWave;
   const int lb = a.light_bound;
   const uint64_t ml = __ballot(n_ent > 0 && n_ent <= lb), mh = __ballot(n_ent > lb);
@@ -1374,7 +1375,7 @@ __global__ __launch_bounds__(kThreads) void k_row_pre(RowArgs<R> a, int4 *__rest
   __syncthreads();
   if (threadIdx.x == 0) {
     int sl = 0, sh = 0;
-    for (int k = 0; k < kThreads / kWave; ++k) {
+    for (int k = 0; k < kPreThreads / kWave; ++k) {
       const int a0 = wl[k], b0 = wh[k];
       wl[k] = sl;
       wh[k] = sh;
@@ -2359,8 +2360,8 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   if (grad || H) {
     prof_mark(c, ST_ROWS_PRE, 0);
     if (c->V)
-      hipLaunchKernelGGL(k_row_pre<R>, dim3(nblk(c->V) + c->n_env), dim3(kThreads), 0, s, ra, b.rlist, b.rcount,
-                         H ? 1 : 0, en, (int)nblk(c->V));
+      hipLaunchKernelGGL(k_row_pre<R>, dim3(nblk(c->V, kPreThreads) + c->n_env), dim3(kPreThreads), 0, s, ra, b.rlist,
+                         b.rcount, H ? 1 : 0, en, (int)nblk(c->V, kPreThreads));
     prof_mark(c, ST_ROWS_PRE, 1);
   }
   // the row kernels walk the two row lists with fixed grids: light rows with
