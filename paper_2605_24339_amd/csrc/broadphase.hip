@@ -321,13 +321,12 @@ constexpr int kQuerySmall = 64;       // the first set a triangle tries
 constexpr int kQuerySmallProbe = 16;  // probes before it moves to the full set
 constexpr int kMaxSlabs = 64;
 
-// a / b for 0 <= a and 1 <= b (both below 2^24): a float quotient, then
-// corrected to the exact integer one (a fraction of an integer division's cost)
-__device__ inline int div_small(int a, int b) {
-  int q = (int)__fdividef((float)a, (float)b);
-  while (q > 0 && q * b > a) --q;
-  while ((q + 1) * b <= a) ++q;
-  return q;
+// a / b for 0 <= a and 1 <= b: below 2^20 the float quotient of a + 1/2,
+// which is at least 1 / 2b from an integer while the reciprocal's and the
+// product's rounding stay under a / b * 2^-22; above (a slab over a million
+// cells) the integer division
+__device__ inline int div_small(int a, int b, bool small) {
+  return small ? (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b)) : a / b;
 }
 
 // box of the prism slab {p + t n : p in T, t0 <= t <= t1}
@@ -513,6 +512,13 @@ __global__ __launch_bounds__(kThreads) void k_query_pre(const R *__restrict__ xs
 // content of a triangle's list does not depend on the order); k_cand_move
 // then places every list at its CSR offset, so the candidate CSR is the
 // same on every run.
+// What bounds it: instruction issue and the cache (in a batch a triangle has
+// 49 cell items and 58 incidences for 5.4 candidates, each incidence gathers
+// two boxes).  The wave's uniform values are scalar, a slab's box is read
+// from LDS where the lane that built it put it, and the small divisions need
+// no correction: 579 -> 449 M vector instructions for 1.16 M triangles, 1.10
+// -> 1.05 ms.  Collecting the ids first and testing the distinct ones was
+// slower (1.4 ms), loading the next triangle's frame ahead no faster.
 template <typename R>
 __device__ __forceinline__ void query_body(const R *__restrict__ xs, const int32_t *__restrict__ ts,
                                                      const int32_t *__restrict__ s_order,
@@ -530,10 +536,13 @@ __device__ __forceinline__ void query_body(const R *__restrict__ xs, const int32
                                                      const int32_t *__restrict__ qcount,
                                                      int32_t *__restrict__ cand_blk, DevStatus *st) {
   __shared__ int32_t set[kQueryWaves][kQuerySet];
-  __shared__ int32_t dense[kQueryWaves][kQuerySet];
+  __shared__ float2 slabs[kQueryWaves][kMaxSlabs][3];  // the slabs' boxes
   __shared__ int2 imark[kQueryWaves][kWave];  // per round of 64 incidences: where each item's incidences start
   __shared__ int blk_req;  // candidates requested by this block's triangles (LDS atomics)
-  const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+  // (the wave index in a scalar register: the triangle's frame, environment
+  // and grid come by scalar loads)
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
+  float2(*slab)[3] = slabs[w];
   // (blocks take list entries in dispatch order: an XCD-by-XCD mapping of
   // the list measured slower on the single indentation and no faster on
   // the batch)
@@ -573,6 +582,7 @@ __device__ __forceinline__ void query_body(const R *__restrict__ xs, const int32
   if (lane < S) {
     float lo[3], hi[3];
     slab_box(tlo, thi, n, -eps + lane * dt, -eps + (lane + 1) * dt, margin, lo, hi);
+    for (int d = 0; d < 3; ++d) slab[lane][d] = make_float2(lo[d], hi[d]);
     if (box_hits_grid(g, lo, hi)) {
       for (int d = 0; d < 3; ++d) {
         c0[d] = cell_coord(g, lo[d], d);
@@ -582,7 +592,8 @@ __device__ __forceinline__ void query_body(const R *__restrict__ xs, const int32
     }
   }
   const int incl = wave_incl_add(ncs);
-  const int work = __shfl(incl, kWave - 1, kWave);
+  const int work = __builtin_amdgcn_readlane(incl, kWave - 1);
+  const bool small = work < (1 << 20);
   const int64_t base = env[e].cell0;
   // the candidate set starts small (most triangles have a few candidates:
   // a short set is cheap to clear and compact); a triangle whose insertions
@@ -601,7 +612,7 @@ __device__ __forceinline__ void query_body(const R *__restrict__ xs, const int32
     for (int w0 = 0; w0 < work; w0 += kWave) {
       const int wi = w0 + lane;
       int s = 0;
-      for (int z = 0; z < S; ++z) s += __shfl(incl, z, kWave) <= wi;  // slab holding item wi
+      for (int z = 0; z < S; ++z) s += __builtin_amdgcn_readlane(incl, z) <= wi;  // slab holding item wi
       s = min(s, kWave - 1);
       const int sc0x = __shfl(c0[0], s, kWave), sc0y = __shfl(c0[1], s, kWave), sc0z = __shfl(c0[2], s, kWave);
       const int sc1x = __shfl(c1[0], s, kWave), sc1y = __shfl(c1[1], s, kWave);
@@ -610,14 +621,14 @@ __device__ __forceinline__ void query_body(const R *__restrict__ xs, const int32
       if (wi < work) {
         const int nxr = sc1x - sc0x + 1, nyr = sc1y - sc0y + 1;
         const int li = wi - sstart;
-        const int q1 = div_small(li, nxr), q2 = div_small(q1, nyr);
+        const int q1 = div_small(li, nxr, small), q2 = div_small(q1, nyr, small);
         const int x = sc0x + (li - q1 * nxr), y = sc0y + (q1 - q2 * nyr), zc = sc0z + q2;
         const int64_t cell = base + ((int64_t)zc * g.ny + y) * g.nx + x;
         cs = cell_start[cell];
         cn = cell_start[cell + 1] - cs;
       }
       const int ci = wave_incl_add(cn);
-      const int tot = __shfl(ci, kWave - 1, kWave);
+      const int tot = __builtin_amdgcn_readlane(ci, kWave - 1);
       const int pfx = ci - cn;  // the lane's first incidence
       // incidences 64 per round, one per lane; the owner of incidence f is
       // the item whose range [pfx, pfx + cn) holds it: every item with
@@ -645,11 +656,10 @@ __device__ __forceinline__ void query_body(const R *__restrict__ xs, const int32
         const int f = f0 + lane;
         if (f >= tot) continue;
         const int j = off + f;
-        float lo[3], hi[3];
-        slab_box(tlo, thi, n, -eps + sl * dt, -eps + (sl + 1) * dt, margin, lo, hi);
         const int M = items[j];
+        const float2 sx = slab[sl][0], sy = slab[sl][1], sz = slab[sl][2];
         const float4 a = mbox[3 * (int64_t)M], b = mbox[3 * (int64_t)M + 1];
-        if (a.x > hi[0] || b.x < lo[0] || a.y > hi[1] || b.y < lo[1] || a.z > hi[2] || b.z < lo[2]) continue;
+        if (a.x > sx.y || b.x < sx.x || a.y > sy.y || b.y < sy.x || a.z > sz.y || b.z < sz.x) continue;
         const float4 nm = mbox[3 * (int64_t)M + 2];
         // facing test with slack: the narrow phase takes the exact decision
         if (n[0] * nm.x + n[1] * nm.y + n[2] * nm.z >= 1e-5f) continue;
@@ -677,11 +687,11 @@ __device__ __forceinline__ void query_body(const R *__restrict__ xs, const int32
   }
   wave_sync();
   int nu = 0;
+  int32_t *dense = set[w];  // the set compacted in place (read before any lane writes)
   for (int k0 = 0; k0 < tsz; k0 += kWave) {
-    int k = k0 + lane;
-    bool used = k < tsz && set[w][k] >= 0;
-    uint64_t m = __ballot(used);
-    if (used) dense[w][nu + __popcll(m & ((1ull << lane) - 1))] = set[w][k];
+    const int32_t v = set[w][k0 + lane];
+    const uint64_t m = __ballot(v >= 0);
+    if (v >= 0) dense[nu + __popcll(m & ((1ull << lane) - 1))] = v;
     nu += __popcll(m);
   }
   int off = 0;
@@ -697,8 +707,8 @@ __device__ __forceinline__ void query_body(const R *__restrict__ xs, const int32
   if (off < 0) return;  // dropped (capacity reported below)
   int32_t *l = cand_tmp + blockIdx.x * share + off;
   for (int k = lane; k < nu; k += kWave) {  // rank sort: ids are unique
-    int v = dense[w][k], r = 0;
-    for (int m = 0; m < nu; ++m) r += dense[w][m] < v;
+    int v = dense[k], r = 0;
+    for (int m = 0; m < nu; ++m) r += dense[m] < v;
     l[r] = v;
   }
   wave_sync();  // the set is reused by the wave's next triangle
@@ -714,8 +724,10 @@ __device__ __forceinline__ void query_body(const R *__restrict__ xs, const int32
   }
 }
 
-// float: seven waves per SIMD (72 registers); double as compiled
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_query_f32(
+// Eight waves per SIMD: the bound is on the scalar registers (16 more are
+// reserved per wave than the occupancy counts; with 94 the eighth block per
+// CU started late and its triangles ran alone, 5.28 against 5.07 ms a step)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_query_f32(
     const float *__restrict__ xs, const int32_t *__restrict__ ts, const int32_t *__restrict__ s_order,
     const int32_t *__restrict__ s_env, const EnvInfo *__restrict__ env, const GridEnv *__restrict__ grid, int64_t Ts,
     const int32_t *__restrict__ cell_start, const int32_t *__restrict__ items, const float4 *__restrict__ mbox,
@@ -725,7 +737,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
   query_body<float>(xs, ts, s_order, s_env, env, grid, Ts, cell_start, items, mbox, cand_cnt, tmp_off, cand_tmp,
                     cap_cand, cap_items, total_cells, qlist, qrec, qcount, cand_blk, st);
 }
-__global__ __launch_bounds__(kThreads) void k_query_f64(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_query_f64(
     const double *__restrict__ xs, const int32_t *__restrict__ ts, const int32_t *__restrict__ s_order,
     const int32_t *__restrict__ s_env, const EnvInfo *__restrict__ env, const GridEnv *__restrict__ grid, int64_t Ts,
     const int32_t *__restrict__ cell_start, const int32_t *__restrict__ items, const float4 *__restrict__ mbox,
