@@ -118,7 +118,7 @@ template <typename R>
 __device__ __forceinline__ void narrow_tile(const NarrowArgs<R> &a, NarrowLds<R> &lds, const int tile_id) {
   constexpr int kNW = narrow_waves<R>();
   auto &nl = lds.nl;
-  const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
   // the block's allocation: every wave calls it once (two block barriers);
   // a wave with records also takes a slot of the active-tile list
   int tslot = -1;
@@ -447,7 +447,7 @@ template <typename R>
 __device__ __forceinline__ void narrow_body(const NarrowArgs<R> &a) {
   constexpr int kNW = narrow_waves<R>();
   __shared__ NarrowLds<R> lds;
-  const int w = threadIdx.x / kWave, count = *a.ntile_cnt, nb = (count + kNW - 1) / kNW;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), count = *a.ntile_cnt, nb = (count + kNW - 1) / kNW;
   // (one turn per block and a block per tile of the mesh: a loop over the
   // list holds registers that the turn needs and spills)
   if (blockIdx.x >= 8 * ((nb + 7) >> 3)) return;
@@ -1452,7 +1452,7 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
                                                            const int32_t *__restrict__ rcount) {
   constexpr int pass = PASS;
   extern __shared__ __align__(16) unsigned char smem[];
-  const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
   const int ecap = HEAVY ? kRowEnt : a.light_bound;
   const size_t per_wave = row_lds_wave<R>(slots, pass, HEAVY, a.light_bound);
   int32_t *key = reinterpret_cast<int32_t *>(smem + (size_t)w * per_wave);
@@ -2492,7 +2492,7 @@ __global__ __launch_bounds__(kThreads) void k_energy_frozen(const R *__restrict_
                                                              const int32_t *__restrict__ tri_rcnt,
                                                              const R *__restrict__ tri_nrm, const DevStatus *st,
                                                              int64_t cap_active, double *__restrict__ tile_E) {
-  const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
   const int tile_id = blockIdx.x * kTilePerBlock + w;
   if (tile_id >= n_tiles) return;
   if ((int64_t)st->n_active > cap_active) {

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kThreads) void k_ccd_linear(const Rec<R> *__restric
   // environment changes; the last one goes through the block reduction)
   int ew = -1;
   float aw = INFINITY;
-  for (int64_t li = (int64_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave; li < nlist;
+  for (int64_t li = (int64_t)blockIdx.x * (kThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave); li < nlist;
        li += (int64_t)gridDim.x * (kThreads / kWave)) {
     const int tile_id = list ? list[li] : (int)li;
     float a = INFINITY;
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(kThreads) void k_ccd_accd(
   __shared__ int32_t plist[kThreads / kWave][kAccdPool];
   __shared__ int32_t pcnt[kThreads / kWave][kWave];
   __shared__ int32_t qpt[kThreads / kWave][2 * kWave], qm[kThreads / kWave][2 * kWave];  // pair queue
-  const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
   const bool grid_ok = cell_start[total_cells] <= cap_items;
   const int64_t nlist = *count;
   // the wave's running minimum of environment ew (flushed when the
