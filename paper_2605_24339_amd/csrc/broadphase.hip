@@ -160,7 +160,8 @@ __device__ inline GridEnv grid_of(const EnvInfo &v, const uint32_t *__restrict__
     if (tot <= v.cell_budget) break;
     h *= 1.05 * cbrt((double)tot / (double)v.cell_budget);
   }
-  g.valid = tot <= v.cell_budget && n[0] < (1 << 30) && n[1] < (1 << 30) && n[2] < (1 << 30);
+  const int f = n[2] < n[0] && n[2] <= n[1] ? 2 : (n[1] < n[0] ? 1 : 0);
+  g.valid = tot <= v.cell_budget && n[0] < (1 << 30) && n[1] < (1 << 30) && n[2] < (1 << 30) ? 1 + f : 0;
   g.h = (float)h;
   g.inv_h = (float)(1.0 / h);
   g.nx = (int)n[0];
@@ -239,7 +240,7 @@ __global__ __launch_bounds__(kThreads) void k_master_boxes(const R *__restrict__
   const int64_t base = env[e].cell0;
   for (int z = c0[2]; z <= c1[2]; ++z)
     for (int y = c0[1]; y <= c1[1]; ++y)
-      for (int x = c0[0]; x <= c1[0]; ++x) atomicAdd(&cell_cnt[base + ((int64_t)z * g.ny + y) * g.nx + x], 1);
+      for (int x = c0[0]; x <= c1[0]; ++x) atomicAdd(&cell_cnt[base + cell_of(g, x, y, z)], 1);
 }
 
 // place the master ids in their cells after the count and its scan (the
@@ -296,7 +297,7 @@ __global__ __launch_bounds__(kThreads) void k_grid_insert(const float4 *__restri
     int slot[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      cell[k] = base + ((int64_t)z * g.ny + y) * g.nx + x;
+      cell[k] = base + cell_of(g, x, y, z);
       x += L;
       while (x > c1[0]) {
         x -= nx;
@@ -424,30 +425,7 @@ __global__ __launch_bounds__(kThreads) void k_query_pre(const R *__restrict__ xs
           if (ncell > 4096) {
             active = true;  // too many cells to count here: let the wave kernel decide
           } else {
-            const int64_t base = env[e].cell0;
-            // the (y, z) rows of the box, 8 at a time so that their loads are
-            // in flight together; a row's x-run of cells is contiguous
-            const int ny = c1[1] - c0[1] + 1, nrow = ny * (c1[2] - c0[2] + 1);
-            int ry = 0, rz = 0;  // row r0 + k as (y, z) offsets, stepped (no divisions)
-            for (int r0 = 0; r0 < nrow && !active; r0 += 8) {
-              int32_t hi_s[8], lo_s[8];
-#pragma unroll
-              for (int k = 0; k < 8; ++k) {
-                const int r = r0 + k;
-                hi_s[k] = lo_s[k] = 0;
-                const int64_t row = base + ((int64_t)(c0[2] + rz) * g.ny + c0[1] + ry) * g.nx;
-                if (++ry == ny) {
-                  ry = 0;
-                  ++rz;
-                }
-                if (r < nrow) {
-                  hi_s[k] = cell_start[row + c1[0] + 1];
-                  lo_s[k] = cell_start[row + c0[0]];
-                }
-              }
-#pragma unroll
-              for (int k = 0; k < 8; ++k) active = active || hi_s[k] > lo_s[k];
-            }
+            active = any_item(g, c0, c1, cell_start + env[e].cell0);
           }
         }
       }
@@ -623,7 +601,7 @@ __device__ __forceinline__ void query_body(const R *__restrict__ xs, const int32
         const int li = wi - sstart;
         const int q1 = div_small(li, nxr, small), q2 = div_small(q1, nyr, small);
         const int x = sc0x + (li - q1 * nxr), y = sc0y + (q1 - q2 * nyr), zc = sc0z + q2;
-        const int64_t cell = base + ((int64_t)zc * g.ny + y) * g.nx + x;
+        const int64_t cell = base + cell_of(g, x, y, zc);
         cs = cell_start[cell];
         cn = cell_start[cell + 1] - cs;
       }

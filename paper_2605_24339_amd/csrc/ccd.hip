@@ -305,30 +305,7 @@ __global__ __launch_bounds__(kThreads) void k_ccd_pre(const R *__restrict__ xs, 
         if (ncell > 4096) {
           active = true;  // too many cells to check here: the CCD kernel decides
         } else {
-          const int64_t base = env[e].cell0;
-          // the (y, z) rows of the box, 8 at a time (their loads in flight
-          // together); a row's x-run of cells is contiguous
-          const int ny = c1[1] - c0[1] + 1, nrow = ny * (c1[2] - c0[2] + 1);
-          int ry = 0, rz = 0;  // row r0 + k as (y, z) offsets, stepped (no divisions)
-          for (int r0 = 0; r0 < nrow && !active; r0 += 8) {
-            int32_t hi_s[8], lo_s[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              const int r = r0 + k;
-              hi_s[k] = lo_s[k] = 0;
-              const int64_t row = base + ((int64_t)(c0[2] + rz) * g.ny + c0[1] + ry) * g.nx;
-              if (++ry == ny) {
-                ry = 0;
-                ++rz;
-              }
-              if (r < nrow) {
-                hi_s[k] = cell_start[row + c1[0] + 1];
-                lo_s[k] = cell_start[row + c0[0]];
-              }
-            }
-#pragma unroll
-            for (int k = 0; k < 8; ++k) active = active || hi_s[k] > lo_s[k];
-          }
+          active = any_item(g, c0, c1, cell_start + env[e].cell0);
         }
       }
     }
@@ -435,7 +412,7 @@ __global__ __launch_bounds__(kThreads) void k_ccd_accd(
       for (int z = c0[2]; z <= c1[2]; ++z)
         for (int y = c0[1]; y <= c1[1]; ++y)
           for (int x = c0[0]; x <= c1[0]; ++x) {
-            const int64_t cell = base + ((int64_t)z * g.ny + y) * g.nx + x;
+            const int64_t cell = base + cell_of(g, x, y, z);
             const int i1 = cell_start[cell + 1];
             for (int i = cell_start[cell] + q; i < i1; i += tl.nq) {
               const int M = items[i];
@@ -544,7 +521,7 @@ __global__ __launch_bounds__(kThreads) void k_ccd_accd(
       for (int z = c0[2]; z <= c1[2]; ++z)
         for (int y = c0[1]; y <= c1[1]; ++y)
           for (int x = c0[0]; x <= c1[0]; ++x) {
-            const int64_t cell = base + ((int64_t)z * g.ny + y) * g.nx + x;
+            const int64_t cell = base + cell_of(g, x, y, z);
             for (int i = cell_start[cell]; i < cell_start[cell + 1]; ++i) {
               const int M = items[i];
               const float4 ma = smbox[3 * (int64_t)M];
