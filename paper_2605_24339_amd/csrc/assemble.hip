@@ -84,20 +84,13 @@ struct NarrowArgs {
   const int32_t *m_opp, *m_vt_off, *m_vt;          // master edge neighbours, vertex adjacency
 };
 
-// Entry of a list of n that virtual block v stands for: the list is split
-// into eight runs, one per XCD (blocks go to the XCDs in turn), so that
-// neighbouring entries share an L2 and every XCD gets an eighth of the work;
-// -1 past the XCD's run.
-__device__ inline int xcd_entry(int v, int n) {
-  const int per = (n + 7) >> 3, at = (v & 7) * per + (v >> 3);
-  return (v >> 3) < per && at < n ? at : -1;
-}
-
 // Narrow phase: one wave per listed work tile, narrow_waves tiles per block.
 // The broad phase lists the tiles with a candidate: a launch over all tiles
-// spent its time on the others (256 environments: 1.22 -> 1.14 ms) and the
-// clustered tiles of one contact patch fell on few XCDs (large indentation
-// 45 -> 41.6 us, its clipped samples 281 -> 231 us).  The records and pairs
+// spent its time on the others (256 environments: 1.22 -> 1.14 ms; large
+// indentation 45 -> 40 us).  The blocks take the list in order: a run of the
+// list per XCD put the heavy tiles, which are neighbours, on few of them
+// (clipped samples of the large indentation 210 us, 163 in order).  The
+// records and pairs
 // of a block are allocated together (wave counts in LDS, one pair of atomics
 // per block), so every wave of a block passes through that allocation
 // exactly once, whatever its tile holds.
@@ -450,9 +443,9 @@ __device__ __forceinline__ void narrow_body(const NarrowArgs<R> &a) {
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), count = *a.ntile_cnt, nb = (count + kNW - 1) / kNW;
   // (one turn per block and a block per tile of the mesh: a loop over the
   // list holds registers that the turn needs and spills)
-  if (blockIdx.x >= 8 * ((nb + 7) >> 3)) return;
-  const int e = xcd_entry(blockIdx.x, nb), i = e * kNW + w;
-  if (e >= 0) narrow_tile<R>(a, lds, i < count ? a.ntile[i] : -1);
+  if ((int)blockIdx.x >= nb) return;
+  const int i = blockIdx.x * kNW + w;
+  narrow_tile<R>(a, lds, i < count ? a.ntile[i] : -1);
 }
 
 // float: six waves per SIMD (80 registers), three blocks of 8 waves per CU
@@ -473,8 +466,10 @@ __global__ __launch_bounds__(kWave * 4) void k_narrow_f64(NarrowArgs<double> a) 
 // in the projected master triangle, gap g = sum_j beta^m_j h_j with h_j the
 // master vertices' heights above T's plane (= n_T . (x_m - x_s), Eq. (gap)),
 // weight w = 2 A_sub W_q with A_sub the sub-triangle's share of T's rest
-// area.  One wave per work tile, the tile's triangles in turn, candidate
-// pairs in chunks of 64: a lane projects and clips one pair, then the
+// area.  kMortarParts waves per work tile, each taking its share of the
+// tile's triangles in turn (the contact patch is few tiles: with one wave per
+// tile half of the card waited for the others: 228 us for the large
+// indentation, 163 so), candidate pairs in chunks of 64: a lane projects and clips one pair, then the
 // chunk's (pair, sub-triangle, rule point) items are spread over the lanes.
 // A counting pass sizes the triangle's records and pairs (one allocation,
 // so they stay contiguous and in candidate order), a writing pass
@@ -626,8 +621,11 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
   __shared__ int32_t candM[kWave];                     // master triangle of each candidate lane
   __shared__ R pacc[18][kWave];                        // each candidate lane's pair sums (mm 6, sm 9, gm 3)
   const int lane = threadIdx.x;
-  const int count = *a.ntile_cnt, entry = blockIdx.x < 8 * ((count + 7) >> 3) ? xcd_entry(blockIdx.x, count) : -1;
-  if (entry < 0) return;
+  // a wave per part of a listed tile; the parts of a tile on one XCD, the
+  // tiles over the XCDs in turn (the heavy ones are neighbours in the list)
+  const int part = (blockIdx.x >> 3) % kMortarParts;
+  const int entry = (int)((blockIdx.x >> 3) / kMortarParts * 8 + (blockIdx.x & 7));
+  if (entry >= *a.ntile_cnt) return;
   const int tile_id = a.ntile[entry];
   const Tile tl = a.tiles[tile_id];
   const EnvInfo &ev = a.env[tl.env];
@@ -643,7 +641,7 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
   R(*fr)[kWave] = reinterpret_cast<R(*)[kWave]>(&poly[1][0][0][0]);
   double E = 0.0;
   const uint64_t below = (1ull << lane) - 1;
-  for (int j = 0; j < tl.count; ++j) {
+  for (int j = part; j < tl.count; j += kMortarParts) {
     const int T = a.s_order[tl.first + j];
     const int cn = a.cand_cnt[T], cb = cn > 0 ? a.cand_pos[T] : 0;
     // support radius of the triangle's samples, Eq. (adaptive_eps): in this
@@ -1062,7 +1060,7 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
     }
   }
   for (int o = 32; o > 0; o >>= 1) E += __shfl_xor(E, o, kWave);
-  if (lane == 0) a.tile_E[tile_id] = E;
+  if (lane == 0) a.tile_E[(int64_t)kMortarParts * tile_id + part] = E;
 }
 
 __global__ __launch_bounds__(kWave) void k_mortar_f32(NarrowArgs<float> a) { mortar_body<float>(a); }
@@ -1278,6 +1276,7 @@ struct EnergyArgs {
   const uint32_t *tile_act, *epoch;  // tile_act (nullable): only the tiles the last broad phase listed have an energy
   const EnvInfo *env;
   R *energy;
+  int parts;  // energies per tile, summed in order
 };
 
 template <typename R, int NT>
@@ -1297,7 +1296,8 @@ __device__ inline void env_energy(const EnergyArgs<R> &a, int e) {
     for (int v = 0; v < kN; ++v) {
       const int t = min(tb + v * NT, t1 - 1);
       act[v] = a.tile_act ? a.tile_act[t] : now;
-      E[v] = a.tile_E[t];
+      E[v] = a.tile_E[(int64_t)a.parts * t];
+      for (int p = 1; p < a.parts; ++p) E[v] += a.tile_E[(int64_t)a.parts * t + p];
     }
 #pragma unroll
     for (int v = 0; v < kN; ++v)
@@ -2293,14 +2293,14 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   prof_mark(c, ST_NARROW, 0);
   if (c->n_tiles) {
     if (c->mortar) {
-      const dim3 mgrid((unsigned)((c->n_tiles + 7) / 8 * 8));
+      const dim3 mgrid((unsigned)((c->n_tiles + 7) / 8 * 8 * kMortarParts));
       if constexpr (sizeof(R) == 4)
         hipLaunchKernelGGL(k_mortar_f32, mgrid, dim3(kWave), 0, s, na);
       else
         hipLaunchKernelGGL(k_mortar_f64, mgrid, dim3(kWave), 0, s, na);
       hipLaunchKernelGGL(k_mortar_counts, dim3(1), dim3(64), 0, s, b.status);
     } else {
-      const dim3 ngrid((nblk(c->n_tiles, narrow_waves<R>()) + 7) / 8 * 8);
+      const dim3 ngrid(nblk(c->n_tiles, narrow_waves<R>()));
       if constexpr (sizeof(R) == 4)
         hipLaunchKernelGGL(k_narrow_f32, ngrid, dim3(kWave * narrow_waves<R>()), 0, s, na);
       else
@@ -2356,7 +2356,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   if (sums && !H) mtri(s);  // the gradient rows read the sums
   // the energies in blocks of the row lists' kernel (one launch less in the
   // chain, 7 us of a small step)
-  const EnergyArgs<R> en{b.tile_E, b.tile_act, b.epoch, b.env, energy};
+  const EnergyArgs<R> en{b.tile_E, b.tile_act, b.epoch, b.env, energy, c->mortar ? kMortarParts : 1};
   if (grad || H) {
     prof_mark(c, ST_ROWS_PRE, 0);
     if (c->V)
@@ -2545,7 +2545,7 @@ hipError_t launch_energy_frozen(gmcp_ctx *c, const R *xs, const R *xm, R *energy
                        c->ts, c->tm, b.tiles, (int)c->n_tiles, b.s_order, b.env, b.rule, (const R *)b.area,
                        (const Rec<R> *)b.rec, b.tri_roff, b.tri_rcnt, (const R *)b.tri_nrm, b.status, c->caps.active,
                        b.tile_E);
-  const EnergyArgs<R> en{b.tile_E, nullptr, nullptr, b.env, energy};
+  const EnergyArgs<R> en{b.tile_E, nullptr, nullptr, b.env, energy, 1};
   hipLaunchKernelGGL(k_energy<R>, dim3(c->n_env), dim3(1024), 0, c->stream, en);
   return hipGetLastError();
 }

@@ -58,6 +58,8 @@ struct GridEnv {           // one environment's uniform grid for this call
   int32_t valid;         // 0, or 1 + the axis along which cells are contiguous
 };
 
+constexpr int kMortarParts = 4;  // waves per work tile of the clipped samples
+
 struct Tile {              // narrow-phase work item: tris [first, first+count) of s_order
   int32_t first, count, env, nq;
 };

@@ -131,7 +131,7 @@ struct Plan {
 struct Sizes {
   int n_env;
   int64_t Vs, Vm, Ts, Tm, Ns, V, n_tiles, cells;
-  bool f64, kin, feat;
+  bool f64, kin, feat, mortar;
 };
 
 bool layout_sizes(const gmcp_layout *L, Sizes *s) {
@@ -142,7 +142,8 @@ bool layout_sizes(const gmcp_layout *L, Sizes *s) {
   s->f64 = (L->flags & GMCP_F64) != 0;
   s->kin = (L->flags & GMCP_KINEMATIC_MASTER) != 0;
   s->feat = (L->flags & GMCP_FEATURES) != 0;
-  if (s->feat && !(L->flags & GMCP_MORTAR)) return false;  // edge / point samples join clipped face samples
+  s->mortar = (L->flags & GMCP_MORTAR) != 0;
+  if (s->feat && !s->mortar) return false;  // edge / point samples join clipped face samples
   if (L->slave_v_off[0] != 0 || L->slave_t_off[0] != 0 || L->master_v_off[0] != 0 ||
       L->master_t_off[0] != 0)
     return false;
@@ -220,7 +221,7 @@ size_t plan_workspace(const Sizes &s, const gmcp_caps &cp, char *base, Buffers *
   t.tri_roff = p.take<int32_t>(s.Ts);
   t.tri_rcnt = p.take<int32_t>(s.Ts);
   t.pair = p.take<char>((s.f64 ? sizeof(Pair<double>) : sizeof(Pair<float>)) * cp.pairs);
-  t.tile_E = p.take<double>(s.n_tiles);
+  t.tile_E = p.take<double>((s.mortar ? kMortarParts : 1) * s.n_tiles);
   t.mp_cnt = p.take<int32_t>(s.Tm + 1);
   t.mp_off = p.take<int32_t>(s.Tm + 1);
   t.mp_list = p.take<int32_t>(cp.pairs);
