@@ -469,8 +469,11 @@ __global__ __launch_bounds__(kWave * 4) void k_narrow_f64(NarrowArgs<double> a) 
 // area.  kMortarParts waves per work tile, each taking its share of the
 // tile's triangles in turn (the contact patch is few tiles: with one wave per
 // tile half of the card waited for the others: 228 us for the large
-// indentation, 163 so), candidate pairs in chunks of 64: a lane projects and clips one pair, then the
-// chunk's (pair, sub-triangle, rule point) items are spread over the lanes.
+// indentation, 163 so; 121 with sums by lane moves, the polygons of a single
+// chunk clipped once, and three waves per SIMD).  What bounds it now: the
+// chain of one triangle with some ten pairs.  Candidate pairs in chunks of
+// 64: a lane projects and clips one pair, then the chunk's (pair,
+// sub-triangle, rule point) items are spread over the lanes.
 // A counting pass sizes the triangle's records and pairs (one allocation,
 // so they stay contiguous and in candidate order), a writing pass
 // recomputes and writes them.  Per triangle and per pair sums, energy:
@@ -609,17 +612,45 @@ __device__ inline bool clip_seg(const R qa[2], const R qb[2], R &t0, R &t1) {
   return t1 > t0;
 }
 
+// Segmented inclusive sums of 18 values over the wave, segments = runs of
+// equal seg >= 0: the steps of wave_incl_add, a lane's source taken only
+// where it is of the lane's segment (lane moves of the vector unit: as
+// shuffles the 19 x 6 LDS round trips were a fifth of a round's time)
+template <int CTRL, int ROWS, typename R>
+__device__ inline void seg_step(int seg, R pt[18]) {
+  const bool take = __builtin_amdgcn_update_dpp(-1, seg, CTRL, ROWS, 0xf, false) == seg;
+#pragma unroll
+  for (int z = 0; z < 18; ++z) {
+    int w[sizeof(R) / 4];
+    R t;
+    __builtin_memcpy(w, &pt[z], sizeof(R));
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(R) / 4); ++k) w[k] = __builtin_amdgcn_update_dpp(0, w[k], CTRL, ROWS, 0xf, false);
+    __builtin_memcpy(&t, w, sizeof(R));
+    pt[z] += take ? t : R(0);
+  }
+}
 template <typename R>
+__device__ inline void seg_scan(int seg, R pt[18]) {
+  seg_step<0x111, 0xf>(seg, pt);  // row_shr:1
+  seg_step<0x112, 0xf>(seg, pt);  // row_shr:2
+  seg_step<0x114, 0xf>(seg, pt);  // row_shr:4
+  seg_step<0x118, 0xf>(seg, pt);  // row_shr:8
+  seg_step<0x142, 0xa>(seg, pt);  // row_bcast:15
+  seg_step<0x143, 0xc>(seg, pt);  // row_bcast:31
+}
+
+template <typename R, bool FEAT>  // FEAT: edge and point samples too
 __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
   __shared__ R poly[2][6][2][kWave];                   // clip buffers (lane-minor); see fr below
   __shared__ uint64_t maskbuf[kMortarChunks][kWave];   // accepted face samples of each lane's pair
-  __shared__ uint32_t fmaskbuf[kMortarChunks][kWave];  // accepted edge (bit 4k + j) / point (bit 12 + k) samples
-  __shared__ uint8_t oflag[kMortarChunks * kWave];     // candidate i of the triangle is opposing
+  __shared__ uint32_t fmaskbuf[FEAT ? kMortarChunks : 1][kWave];  // accepted edge (bit 4k + j) / point (bit 12 + k) samples
+  __shared__ uint8_t oflag[FEAT ? kMortarChunks * kWave : 1];     // candidate i of the triangle is opposing
   __shared__ uint64_t accw[kWave];                     // accepted face items of a chunk, 64 per word
   __shared__ int32_t istart[kWave + 1];                // first face item of each candidate lane of a chunk
   __shared__ int32_t rstart[kWave];                    // first record of each candidate lane (from the triangle's)
   __shared__ int32_t candM[kWave];                     // master triangle of each candidate lane
-  __shared__ R pacc[18][kWave];                        // each candidate lane's pair sums (mm 6, sm 9, gm 3)
+  __shared__ int32_t cids[FEAT ? kMortarChunks * kWave : 1];  // the triangle's candidate ids
   const int lane = threadIdx.x;
   // a wave per part of a listed tile; the parts of a tile on one XCD, the
   // tiles over the XCDs in turn (the heavy ones are neighbours in the list)
@@ -632,9 +663,9 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
   const R dhat = (R)ev.dhat, kappa = (R)ev.kappa, deltaT = (R)ev.delta_T;
   const R kappa_e = (R)ev.kappa_e, kappa_p = (R)ev.kappa_p, delta_e = (R)ev.delta_e;
   const int nq = ev.nq, ng = ev.rule_n;
+  const float inv_nq = 1.0f / (float)nq;
   const double *rule = a.rule + (ev.rule_n - 1) * 16 * 3;
   const double *gl = a.rule + kGaussOff + (ev.rule_n - 1) * 4 * 2;
-  const bool features = a.features;
   R(*buf)[6][2][kWave] = poly;
   // once a lane's clip is done its column of buffer 1 is free: it holds the
   // pair's frame there, fr[z][lane] = q0 (2), qi (4), h (3)
@@ -682,12 +713,9 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
     auto pair_of = [&](int M) { return mortar_pair(a, M, s0, e1, e2, n, gi11, gi12, gi22, eps); };
 
     // ---- feature ownership: an edge or vertex belongs to the smallest-index
-    // opposing candidate master triangle that contains it.  The counting
-    // pass searches the triangle's candidate ids in LDS (the pair sums'
-    // array, which only the writing pass uses)
-    int32_t *cids = reinterpret_cast<int32_t *>(&pacc[0][0]);
-    static_assert(sizeof(pacc) >= sizeof(int32_t) * kMortarChunks * kWave, "candidate ids fit the pair sums");
-    if (features) {
+    // opposing candidate master triangle that contains it (its id searched
+    // in LDS)
+    if (FEAT) {
       wave_sync();
       for (int ci = lane; ci < cn && ci < kMortarChunks * kWave; ci += kWave) {
         const int M = a.cand[cb + ci];
@@ -768,15 +796,11 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
         fr[8][lane] = P.h[2];
       }
       const int ni = m >= 3 ? (m - 2) * nq : 0;
-      int incl = ni;
-      for (int d = 1; d < kWave; d <<= 1) {
-        const int v = __shfl_up(incl, d, kWave);
-        if (lane >= d) incl += v;
-      }
+      const int incl = wave_incl_add(ni);
       istart[lane] = incl - ni;
       if (lane == kWave - 1) istart[kWave] = incl;
       wave_sync();
-      return __shfl(incl, kWave - 1, kWave);
+      return __builtin_amdgcn_readlane(incl, kWave - 1);
     };
     auto item_of = [&](int f, int &cl, int &s, int &qq) -> int {  // f < the chunk's item count
       int lo = 0, hi = kWave - 1;  // the last lane whose items start at or before f
@@ -787,7 +811,7 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
       }
       cl = lo;
       const int local = f - istart[lo];
-      s = local / nq + 1;
+      s = (int)(((float)local + 0.5f) * inv_nq) + 1;  // exact: local < 64, nq <= 16
       qq = local - (s - 1) * nq;
       return local;
     };
@@ -813,7 +837,7 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
     };
 
     // ---- counting pass: accepted samples per candidate pair (bit masks)
-    int nrec = 0, npair = 0;
+    int nrec = 0, npair = 0, tot1 = 0;
     bool pen = false;
     for (int ch = 0; ch < nchunk && ch < kMortarChunks; ++ch) {
       const int ci = ch * kWave + lane;
@@ -825,9 +849,10 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
       if (ci < cn) {
         M = a.cand[cb + ci];
         P = pair_of(M);
-        if (features && P.opposing) fmask = feature_mask(P, M, pen);
+        if (FEAT && P.opposing) fmask = feature_mask(P, M, pen);
       }
       const int tot = chunk_items(P, P.ok);
+      tot1 = tot;
       for (int f0 = 0; f0 < tot; f0 += kWave) {
         const int f = f0 + lane;
         bool acc = false;
@@ -855,13 +880,11 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
         }
       }
       maskbuf[ch][lane] = mask;
-      fmaskbuf[ch][lane] = fmask;
+      if (FEAT) fmaskbuf[ch][lane] = fmask;
       const int cntl = __popcll(mask) + __popc(fmask);
       const uint64_t pm = __ballot(cntl > 0);
       npair += __popcll(pm);
-      int tot_r = cntl;
-      for (int o = 32; o > 0; o >>= 1) tot_r += __shfl_xor(tot_r, o, kWave);
-      nrec += tot_r;
+      nrec += __builtin_amdgcn_readlane(wave_incl_add(cntl), kWave - 1);
       wave_sync();  // the chunk's polygons, frames and words are reused by the next
     }
     if (__any(pen) && lane == 0) set_error(a.st, GMCP_E_PENETRATION, (unsigned long long)T);
@@ -948,17 +971,13 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
     for (int ch = 0; ch < nchunk && ch < kMortarChunks; ++ch) {
       const int ci = ch * kWave + lane;
       const uint64_t mask = maskbuf[ch][lane];
-      const uint32_t fmask = fmaskbuf[ch][lane];
+      const uint32_t fmask = FEAT ? fmaskbuf[ch][lane] : 0;
       const int cntl = __popcll(mask) + __popc(fmask);
-      int incl = cntl;
-      for (int d = 1; d < kWave; d <<= 1) {
-        const int v = __shfl_up(incl, d, kWave);
-        if (lane >= d) incl += v;
-      }
+      const int incl = wave_incl_add(cntl);
       const uint64_t pm = __ballot(cntl > 0);
       const unsigned long long r0 = roff + (unsigned long long)(incl - cntl);  // this pair's first record
       const unsigned long long pslot = poff + __popcll(pm & below);
-      roff += __shfl(incl, kWave - 1, kWave);
+      roff += __builtin_amdgcn_readlane(incl, kWave - 1);
       poff += __popcll(pm);
       int M = -1;
       MortarPair<R> P;
@@ -966,15 +985,20 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
       P.opposing = false;
       if (cntl > 0) {
         M = a.cand[cb + ci];
-        if (mask) P = pair_of(M);
+        if (mask && nchunk > 1) P = pair_of(M);
       }
       candM[lane] = M;
       rstart[lane] = (int32_t)(r0 - rbase);
-      const int tot = chunk_items(P, mask != 0);  // pairs with face samples only
+      // the polygons of a single chunk are still in LDS from the counting
+      // pass; of several, those with face samples are clipped again
+      int tot = tot1;
+      if (nchunk > 1) tot = chunk_items(P, mask != 0);
+      else wave_sync();
       // face samples over the lanes; each pair's sums are segmented scans
       // over the lanes of its items (items of a pair are contiguous), taken
       // by the pair's own lane from the last of them: fixed order
-      for (int z = 0; z < 18; ++z) pacc[z][lane] = R(0);
+      R pacc[18];  // the lane's pair sums (mm 6, sm 9, gm 3)
+      for (int z = 0; z < 18; ++z) pacc[z] = R(0);
       for (int f0 = 0; f0 < tot; f0 += kWave) {
         const int f = f0 + lane;
         int seg = kWave + lane;  // idle lanes: segments of their own
@@ -996,20 +1020,13 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
                  kappa * R(2) * (a2 * area) * wq * gam, kappa, gam, pt);
           }
         }
-        for (int d = 1; d < kWave; d <<= 1) {
-          const int su = __shfl_up(seg, d, kWave);
-          const bool take = lane >= d && su == seg;
-          for (int z = 0; z < 18; ++z) {
-            const R t = __shfl_up(pt[z], d, kWave);
-            if (take) pt[z] += t;
-          }
-        }
+        seg_scan(seg, pt);
         const int i0 = istart[lane], i1 = istart[lane + 1];
         const bool mine = i1 > i0 && i1 > f0 && i0 < f0 + kWave;
         const int src = mine ? min(i1, f0 + kWave) - 1 - f0 : lane;
         for (int z = 0; z < 18; ++z) {
           const R t = __shfl(pt[z], src, kWave);
-          if (mine) pacc[z][lane] += t;
+          if (mine) pacc[z] += t;
         }
       }
       if (cntl > 0) {
@@ -1017,10 +1034,10 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
         pr.T = T;
         pr.M = M;
         for (int m = 0; m < 3; ++m) pr.mv[m] = a.tm[3 * (int64_t)M + m];
-        for (int z = 0; z < 6; ++z) pr.mm[z] = pacc[z][lane];
-        for (int z = 0; z < 9; ++z) pr.sm[z] = pacc[6 + z][lane];
-        for (int z = 0; z < 3; ++z) pr.gm[z] = pacc[15 + z][lane];
-        if (fmask) {
+        for (int z = 0; z < 6; ++z) pr.mm[z] = pacc[z];
+        for (int z = 0; z < 9; ++z) pr.sm[z] = pacc[6 + z];
+        for (int z = 0; z < 3; ++z) pr.gm[z] = pacc[15 + z];
+        if (FEAT && fmask) {
           const MortarPair<R> Q = pair_of(M);
           unsigned long long r = r0 + __popcll(mask);
           for (uint32_t bits = fmask; bits; bits &= bits - 1) {
@@ -1063,8 +1080,14 @@ __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
   if (lane == 0) a.tile_E[(int64_t)kMortarParts * tile_id + part] = E;
 }
 
-__global__ __launch_bounds__(kWave) void k_mortar_f32(NarrowArgs<float> a) { mortar_body<float>(a); }
-__global__ __launch_bounds__(kWave) void k_mortar_f64(NarrowArgs<double> a) { mortar_body<double>(a); }
+template <bool FEAT>
+__global__ __launch_bounds__(kWave) void k_mortar_f32(NarrowArgs<float> a) {
+  mortar_body<float, FEAT>(a);
+}
+template <bool FEAT>
+__global__ __launch_bounds__(kWave) void k_mortar_f64(NarrowArgs<double> a) {
+  mortar_body<double, FEAT>(a);
+}
 
 // ---------------------------------------------------- pairs by master tri
 // pass 0: count pairs per master triangle; pass 1: place (slave triangle,
@@ -1276,7 +1299,7 @@ struct EnergyArgs {
   const uint32_t *tile_act, *epoch;  // tile_act (nullable): only the tiles the last broad phase listed have an energy
   const EnvInfo *env;
   R *energy;
-  int parts;  // energies per tile, summed in order
+  bool parts;  // kMortarParts energies per tile (summed in order), else one
 };
 
 template <typename R, int NT>
@@ -1296,8 +1319,14 @@ __device__ inline void env_energy(const EnergyArgs<R> &a, int e) {
     for (int v = 0; v < kN; ++v) {
       const int t = min(tb + v * NT, t1 - 1);
       act[v] = a.tile_act ? a.tile_act[t] : now;
-      E[v] = a.tile_E[(int64_t)a.parts * t];
-      for (int p = 1; p < a.parts; ++p) E[v] += a.tile_E[(int64_t)a.parts * t + p];
+      if (a.parts) {
+        static_assert(kMortarParts == 4, "two pairs");
+        const double2 *q = reinterpret_cast<const double2 *>(a.tile_E) + 2 * (int64_t)t;
+        const double2 q0 = q[0], q1 = q[1];
+        E[v] = ((q0.x + q0.y) + q1.x) + q1.y;
+      } else {
+        E[v] = a.tile_E[t];
+      }
     }
 #pragma unroll
     for (int v = 0; v < kN; ++v)
@@ -2295,9 +2324,9 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     if (c->mortar) {
       const dim3 mgrid((unsigned)((c->n_tiles + 7) / 8 * 8 * kMortarParts));
       if constexpr (sizeof(R) == 4)
-        hipLaunchKernelGGL(k_mortar_f32, mgrid, dim3(kWave), 0, s, na);
+        hipLaunchKernelGGL(c->features ? k_mortar_f32<true> : k_mortar_f32<false>, mgrid, dim3(kWave), 0, s, na);
       else
-        hipLaunchKernelGGL(k_mortar_f64, mgrid, dim3(kWave), 0, s, na);
+        hipLaunchKernelGGL(c->features ? k_mortar_f64<true> : k_mortar_f64<false>, mgrid, dim3(kWave), 0, s, na);
       hipLaunchKernelGGL(k_mortar_counts, dim3(1), dim3(64), 0, s, b.status);
     } else {
       const dim3 ngrid(nblk(c->n_tiles, narrow_waves<R>()));
@@ -2356,7 +2385,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   if (sums && !H) mtri(s);  // the gradient rows read the sums
   // the energies in blocks of the row lists' kernel (one launch less in the
   // chain, 7 us of a small step)
-  const EnergyArgs<R> en{b.tile_E, b.tile_act, b.epoch, b.env, energy, c->mortar ? kMortarParts : 1};
+  const EnergyArgs<R> en{b.tile_E, b.tile_act, b.epoch, b.env, energy, c->mortar};
   if (grad || H) {
     prof_mark(c, ST_ROWS_PRE, 0);
     if (c->V)
@@ -2545,7 +2574,7 @@ hipError_t launch_energy_frozen(gmcp_ctx *c, const R *xs, const R *xm, R *energy
                        c->ts, c->tm, b.tiles, (int)c->n_tiles, b.s_order, b.env, b.rule, (const R *)b.area,
                        (const Rec<R> *)b.rec, b.tri_roff, b.tri_rcnt, (const R *)b.tri_nrm, b.status, c->caps.active,
                        b.tile_E);
-  const EnergyArgs<R> en{b.tile_E, nullptr, nullptr, b.env, energy, 1};
+  const EnergyArgs<R> en{b.tile_E, nullptr, nullptr, b.env, energy, false};
   hipLaunchKernelGGL(k_energy<R>, dim3(c->n_env), dim3(1024), 0, c->stream, en);
   return hipGetLastError();
 }
