@@ -1125,21 +1125,34 @@ __global__ void k_pair_bucket(const Pair<R> *__restrict__ pair, const DevStatus 
 constexpr int kPairBlocks = 4096;  // grid of the walks over the pairs at most
 
 // deterministic order inside each bucket: every key is ranked among its
-// bucket's keys (slave triangle, unique per bucket) and written in place
+// bucket's keys (slave triangle, unique per bucket) and written in place;
+// threads i, i + step, ... of the walk
 template <typename R>
-__global__ void k_bucket_rank(const Pair<R> *__restrict__ pair, const int32_t *__restrict__ mp_off,
-                              const long long *__restrict__ mp_key, int32_t *__restrict__ mp_list,
-                              const DevStatus *st, int64_t cap_pairs) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t np = (int64_t)st->n_pairs;
-  if (np > cap_pairs) return;
-  for (; i < np; i += (int64_t)gridDim.x * blockDim.x) {
-    const long long key = mp_key[i];
-    const int M = pair[key & 0xffffffffLL].M;
-    int b = mp_off[M], e = mp_off[M + 1], r = 0;
-    for (int j = b; j < e; ++j) r += mp_key[j] < key;
-    mp_list[b + r] = (int32_t)(key & 0xffffffffLL);
+struct RankArgs {
+  const Pair<R> *pair;
+  const int32_t *mp_off;
+  const long long *mp_key;
+  int32_t *mp_list;
+  const DevStatus *st;
+  int64_t cap_pairs;
+};
+
+template <typename R>
+__device__ inline void rank_pairs(const RankArgs<R> &a, int64_t i, int64_t step) {
+  const int64_t np = (int64_t)a.st->n_pairs;
+  if (np > a.cap_pairs) return;
+  for (; i < np; i += step) {
+    const long long key = a.mp_key[i];
+    const int M = a.pair[key & 0xffffffffLL].M;
+    int b = a.mp_off[M], e = a.mp_off[M + 1], r = 0;
+    for (int j = b; j < e; ++j) r += a.mp_key[j] < key;
+    a.mp_list[b + r] = (int32_t)(key & 0xffffffffLL);
   }
+}
+
+template <typename R>
+__global__ void k_bucket_rank(RankArgs<R> a) {
+  rank_pairs(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
 }
 
 template <typename R>
@@ -1358,9 +1371,17 @@ constexpr int kPreThreads = 512;  // (with 256 the energies of one large environ
 template <typename R>
 __global__ __launch_bounds__(kPreThreads) void k_row_pre(RowArgs<R> a, int4 *__restrict__ rlist,
                                                        int32_t *__restrict__ rcount, int zero_cnt,
-                                                       EnergyArgs<R> en, int row_blocks) {
+                                                       EnergyArgs<R> en, int row_blocks, RankArgs<R> rank,
+                                                       int rank_blocks) {
+  // neither the energies nor (with rank_blocks) the order inside the buckets
+  // depends on the row lists: blocks of their own in this launch (a launch
+  // each lengthened a small step by 7 and 5 us)
   if ((int)blockIdx.x >= row_blocks) {
-    env_energy<R, kPreThreads>(en, blockIdx.x - row_blocks);
+    const int b = (int)blockIdx.x - row_blocks;
+    if (b < rank_blocks)
+      rank_pairs(rank, (int64_t)b * kPreThreads + threadIdx.x, (int64_t)rank_blocks * kPreThreads);
+    else
+      env_energy<R, kPreThreads>(en, b - rank_blocks);
     return;
   }
   const int64_t row = (int64_t)blockIdx.x * kPreThreads + threadIdx.x;
@@ -2348,8 +2369,13 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_pair_bucket<R>, dim3(pb), dim3(kThreads), 0, s, pr, b.status, c->caps.pairs, b.mp_cnt,
                      b.mp_off, b.mp_key, c->Tm);
-  hipLaunchKernelGGL(k_bucket_rank<R>, dim3(pb), dim3(kThreads), 0, s, pr, b.mp_off, b.mp_key, b.mp_list, b.status,
-                     c->caps.pairs);
+  const RankArgs<R> rank{pr, b.mp_off, b.mp_key, b.mp_list, b.status, c->caps.pairs};
+  // The order inside the buckets is read by the master-triangle sums: before
+  // the rows of a gradient alone, beside the row counts on the second stream
+  // where the rows are split, else in the row lists' launch
+  const bool split = c->V >= kSplitRows, rank_first = !H || !c->V, rank_beside = !rank_first && split;
+  auto rank_on = [&](hipStream_t st) { hipLaunchKernelGGL(k_bucket_rank<R>, dim3(pb), dim3(kThreads), 0, st, rank); };
+  if (rank_first) rank_on(s);
   prof_mark(c, ST_BUCKET, 1);
   RowArgs<R> ra = row_args<R>(c, H);
   ra.grad = grad;
@@ -2359,9 +2385,9 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   // second stream, forked after the row lists and joined before what reads
   // both (not while profiling).  Few rows: one launch on one stream walks both
   // lists; a fork and its join cost more than a row kernel takes there.
-  // One launch against two (step): 931 rows 195 and 300 us (enqueued one by
-  // one), 9136 rows 173.5 and 186.5, 36893 rows 263 and 249.
-  ra.split = c->V >= kSplitRows;
+  // One launch against two (step): 931 rows 185 and 292 us (enqueued one by
+  // one), 9136 rows 165 and 177, 36893 rows 242 and 229.
+  ra.split = split;
   const bool par = ra.split && c->side != nullptr && !c->prof.on;
   const hipStream_t hs = par ? c->side : s;
   auto fork = [&]() {
@@ -2383,14 +2409,15 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     prof_mark(c, ST_MTRI, 1);
   };
   if (sums && !H) mtri(s);  // the gradient rows read the sums
-  // the energies in blocks of the row lists' kernel (one launch less in the
-  // chain, 7 us of a small step)
+  const unsigned rank_blocks =
+      rank_first || rank_beside ? 0
+                                : (unsigned)std::min<int64_t>(nblk(c->caps.pairs, kPreThreads), kPairBlocks / 2);
   const EnergyArgs<R> en{b.tile_E, b.tile_act, b.epoch, b.env, energy, c->mortar};
   if (grad || H) {
     prof_mark(c, ST_ROWS_PRE, 0);
     if (c->V)
-      hipLaunchKernelGGL(k_row_pre<R>, dim3(nblk(c->V, kPreThreads) + c->n_env), dim3(kPreThreads), 0, s, ra, b.rlist,
-                         b.rcount, H ? 1 : 0, en, (int)nblk(c->V, kPreThreads));
+      hipLaunchKernelGGL(k_row_pre<R>, dim3(nblk(c->V, kPreThreads) + rank_blocks + c->n_env), dim3(kPreThreads), 0, s,
+                         ra, b.rlist, b.rcount, H ? 1 : 0, en, (int)nblk(c->V, kPreThreads), rank, (int)rank_blocks);
     prof_mark(c, ST_ROWS_PRE, 1);
   }
   // the row kernels walk the two row lists with fixed grids: light rows with
@@ -2426,6 +2453,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
                        b.rlist, b.rcount);
     prof_mark(c, ST_ROWS_COUNT_H, 1);
     if ((e = mark_side()) != hipSuccess) return e;
+    if (rank_beside) rank_on(hs);
     if (sums) mtri(hs);  // read by the writing pass, beside the scan
     prof_mark(c, ST_ROWS_COUNT, 0);
     if (ra.split)
@@ -2436,7 +2464,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     e = scan_exclusive(c, b.row_cnt, H->row_ptr, c->V + 1);
     if (e != hipSuccess) return e;
     if ((e = fork()) != hipSuccess) return e;
-    if (sums && (e = join()) != hipSuccess) return e;  // the sums
+    if ((e = join()) != hipSuccess) return e;  // the sums
     prof_mark(c, ST_ROWS_FILL_H, 0);
     hipLaunchKernelGGL((k_rows<R, 1, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 1, true), hs, ra, hslots,
                        b.rlist, b.rcount);
