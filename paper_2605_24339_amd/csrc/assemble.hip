@@ -90,10 +90,9 @@ struct NarrowArgs {
 // indentation 45 -> 40 us).  The blocks take the list in order: a run of the
 // list per XCD put the heavy tiles, which are neighbours, on few of them
 // (clipped samples of the large indentation 210 us, 163 in order).  The
-// records and pairs
-// of a block are allocated together (wave counts in LDS, one pair of atomics
-// per block), so every wave of a block passes through that allocation
-// exactly once, whatever its tile holds.
+// records and pairs of a block are allocated together (wave counts in LDS,
+// one pair of atomics per block), so every wave of a block passes through
+// that allocation exactly once, whatever its tile holds.
 template <typename R> constexpr int narrow_waves() { return sizeof(R) == 4 ? 8 : 4; }
 
 template <typename R>
@@ -644,7 +643,8 @@ template <typename R, bool FEAT>  // FEAT: edge and point samples too
 __device__ __forceinline__ void mortar_body(const NarrowArgs<R> &a) {
   __shared__ R poly[2][6][2][kWave];                   // clip buffers (lane-minor); see fr below
   __shared__ uint64_t maskbuf[kMortarChunks][kWave];   // accepted face samples of each lane's pair
-  __shared__ uint32_t fmaskbuf[FEAT ? kMortarChunks : 1][kWave];  // accepted edge (bit 4k + j) / point (bit 12 + k) samples
+  // accepted edge (bit 4k + j) / point (bit 12 + k) samples
+  __shared__ uint32_t fmaskbuf[FEAT ? kMortarChunks : 1][kWave];
   __shared__ uint8_t oflag[FEAT ? kMortarChunks * kWave : 1];     // candidate i of the triangle is opposing
   __shared__ uint64_t accw[kWave];                     // accepted face items of a chunk, 64 per word
   __shared__ int32_t istart[kWave + 1];                // first face item of each candidate lane of a chunk
@@ -1469,9 +1469,11 @@ __global__ __launch_bounds__(kPreThreads) void k_row_pre(RowArgs<R> a, int4 *__r
 // What bounds it: the light rows of a batch the instructions of their hash
 // probes and rankings, a heavy row and a small scene the chain of one row
 // (LDS round trips of the probes, the blocks' loads).  256 environments,
-// f32, 561 k rows: fill 1.05 ms light with 0.63 ms heavy beside it (before
-// the masks, the three probes together and the blocks two at a time 1.30 and
-// 1.55), count 0.36 and 0.22 ms.
+// f32, 561 k rows: fill 0.97 ms light with 0.89 ms heavy beside it (before
+// the masks, the three probes together, the blocks two at a time and the
+// scalar row index 1.30 and 1.55), count 0.51 and 0.25 ms beside the
+// master-triangle sums and the step bound's sample part (0.35 and 0.15 ms
+// after the sums, alone).
 constexpr int kRowEnt = 512;     // contribution stash of heavy rows (light rows: their bound)
 // incident triangles of a row taken per chunk (kept in LDS): a vertex has
 // far fewer than 32 in the common case, and the smaller table lets more
@@ -2161,7 +2163,8 @@ __global__ void k_pair_export(const Pair<R> *__restrict__ pair, const DevStatus 
 // its records once per pair took 81 us under one large indentation.
 constexpr int kHvpLanes = 16;
 template <typename R>
-__global__ __launch_bounds__(kThreads) void k_hvp_tri(const Rec<R> *__restrict__ rec, const int32_t *__restrict__ tri_roff,
+__global__ __launch_bounds__(kThreads) void k_hvp_tri(const Rec<R> *__restrict__ rec,
+                          const int32_t *__restrict__ tri_roff,
                           const int32_t *__restrict__ tri_rcnt, const int32_t *__restrict__ tri_npair,
                           const int32_t *__restrict__ tri_poff, const Pair<R> *__restrict__ pair,
                           const R *__restrict__ tri_nrm, const int32_t *__restrict__ ts,
@@ -2496,7 +2499,8 @@ hipError_t launch_hvp(gmcp_ctx *c, const R *vx, const R *vd, R *ox, R *od) {
   if (od) hipLaunchKernelGGL(k_fill_r<R>, dim3(nblk(c->Ns) > 4096 ? 4096 : nblk(c->Ns)), dim3(kThreads), 0, s, od,
                              R(0), c->Ns);
   if (c->Ts)
-    hipLaunchKernelGGL(k_hvp_tri<R>, dim3(nblk(kHvpLanes * c->Ts)), dim3(kThreads), 0, s, (const Rec<R> *)b.rec, b.tri_roff,
+    hipLaunchKernelGGL(k_hvp_tri<R>, dim3(nblk(kHvpLanes * c->Ts)), dim3(kThreads), 0, s, (const Rec<R> *)b.rec,
+                       b.tri_roff,
                        b.tri_rcnt, b.tri_npair, b.tri_poff, (const Pair<R> *)b.pair, (const R *)b.tri_nrm, c->ts,
                        c->tm, b.s_env, b.env, b.rule, c->Ts, c->Vs, c->kinematic, vx, vd, od, (R *)b.hv_tri,
                        (R *)b.hv_pair, b.status, c->caps.active, c->caps.pairs);

@@ -190,9 +190,9 @@ __device__ inline bool box_hits_grid(const GridEnv &g, const float lo[3], const 
 // wave derives the grids of its triangles' environments, consecutive ones,
 // for the block, so no separate launch is needed - every thread deriving its
 // own spent 328 double instructions per wave: 181 us for 256 environments,
-// 121 so and with a vertex per load), master triangle boxes (and unit normals), static or swept over
-// dx, and the count of the grid cells each box covers (placement:
-// k_grid_insert)
+// 121 so and with a vertex per load), master triangle boxes (and unit
+// normals), static or swept over dx, and the count of the grid cells each box
+// covers (placement: k_grid_insert)
 template <typename R>
 __global__ __launch_bounds__(kThreads) void k_master_boxes(const R *__restrict__ xm, const R *__restrict__ dxm,
                                                             const int32_t *__restrict__ tm, int64_t Tm,

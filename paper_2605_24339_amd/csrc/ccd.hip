@@ -88,7 +88,8 @@ __global__ __launch_bounds__(kThreads) void k_ccd_linear(const Rec<R> *__restric
   // environment changes; the last one goes through the block reduction)
   int ew = -1;
   float aw = INFINITY;
-  for (int64_t li = (int64_t)blockIdx.x * (kThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave); li < nlist;
+  const int w0 = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  for (int64_t li = (int64_t)blockIdx.x * (kThreads / kWave) + w0; li < nlist;
        li += (int64_t)gridDim.x * (kThreads / kWave)) {
     const int tile_id = list ? list[li] : (int)li;
     float a = INFINITY;

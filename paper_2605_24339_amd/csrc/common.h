@@ -147,7 +147,7 @@ enum Stage {
   ST_QUERY_FILL,   // kernel k_cand_move (scratch lists to the CSR)
   ST_NARROW,       // kernel k_narrow: narrow phase + barrier + sums
   ST_BUCKET,       // pairs bucketed by master triangle (count, scan, place, sort)
-  ST_GRAD,         // kernel k_grad: gradient rows
+  ST_GRAD,         // k_rows pass 2: gradient rows alone
   ST_ROWS_COUNT,   // kernel k_rows, counting pass (light rows)
   ST_ROWS_FILL,    // kernel k_rows, writing pass (light rows)
   ST_CCD_LINEAR,   // kernel k_ccd_linear

@@ -571,8 +571,8 @@ __device__ inline void best8(double &d, int32_t &id) {
 // 13.6 ms by the scan); 2562 vertices: 93 us (3.6 ms).  A wave walking with
 // 64 sorted vertices together, nodes and triangles by scalar loads, took
 // 331 us there but 890 us for the 2562 vertices.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_tree_query(const double *__restrict__ P, int64_t N,
-                                                    const double *__restrict__ V, const int32_t *__restrict__ F,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_tree_query(
+    const double *__restrict__ P, int64_t N, const double *__restrict__ V, const int32_t *__restrict__ F,
                                                     TreeDev t, int32_t *__restrict__ tri, double *__restrict__ bary,
                                                     double *__restrict__ delta, double *__restrict__ dist2) {
   __shared__ float kept[kMaxLevels - 1][256];  // d of the levels above: kept[l] is level l + 1's
