@@ -330,21 +330,32 @@ class Context:
             A = self.assemble(xs, xm, check=check)
             alpha = self.ccd_step(xs, xm, dxs, dxm, check=check)
             return A, alpha
+        xs = self._x(xs, self.Vs, "x_slave")
+        xm = self._x(xm, self.Vm, "x_master")
+        dxs = self._x(dxs, self.Vs, "dx_slave")
+        dxm = self._x(dxm, self.Vm, "dx_master")
         main = torch.cuda.current_stream(self.device)
         if self._side is None:
             self._side = torch.cuda.Stream(self.device)  # default priority
+            self._fork, self._join = torch.cuda.Event(), torch.cuda.Event()
+        # the library's stream is set directly: torch enqueues nothing here, and
+        # switching its own stream and waiting by new events took 30 us a step
+        lib, ctx, side = N.lib(), self._ctx, C.c_void_p(self._side.cuda_stream)
         self.broadphase(xs, xm, check=False)
-        self._side.wait_stream(main)
-        with torch.cuda.stream(self._side):
-            self.ccd_swept(xs, xm, dxs, dxm)
-        A = self.assemble(xs, xm, check=False)
-        with torch.cuda.stream(self._side):
+        self._fork.record(main)
+        self._side.wait_event(self._fork)
+        try:
+            _check(lib.gmcp_set_stream(ctx, side), "gmcp_set_stream")
+            _check(lib.gmcp_ccd_swept(ctx, _ptr(xs), _ptr(xm), _ptr(dxs), _ptr(dxm)), "gmcp_ccd_swept")
+            A = self.assemble(xs, xm, check=False)
+            _check(lib.gmcp_set_stream(ctx, side), "gmcp_set_stream")
+            _check(lib.gmcp_wait_samples(ctx), "gmcp_wait_samples")
+            _check(lib.gmcp_ccd_finish(ctx, _ptr(dxs), _ptr(dxm), _ptr(self.alpha)), "gmcp_ccd_finish")
+        finally:  # also after an error: later calls (``status``) follow the caller's stream
             self._bind()
-            _check(N.lib().gmcp_wait_samples(self._ctx), "gmcp_wait_samples")
-            alpha = self.ccd_finish(dxs, dxm)
-        main.wait_stream(self._side)
-        self._bind()  # later calls (``status``) follow the caller's stream again
-        return A, alpha
+            self._join.record(self._side)
+            main.wait_event(self._join)
+        return A, self.alpha
 
     def capture(self, xs, xm, dxs, dxm=None) -> "torch.cuda.CUDAGraph":
         """Capture one full step into a HIP graph.  ``graph.replay()`` re-runs
