@@ -1253,13 +1253,12 @@ __device__ inline R quad_sum(R v) {
 // sums the pairs s, s + 4, ... in order (their loads issued four at a time),
 // and the four partials are combined by a fixed butterfly, so the result is
 // the same on every run.
-template <typename R>
-__global__ __launch_bounds__(kThreads) void k_mtri(const Pair<R> *__restrict__ pair,
-                                                    const int32_t *__restrict__ mp_off,
-                                                    const int32_t *__restrict__ mp_list,
-                                                    const R *__restrict__ tri_nrm, int64_t Tm, const DevStatus *st,
-                                                    int64_t cap_pairs, R *__restrict__ mtri) {
-  const int64_t gt = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+template <typename R, int NT>
+__device__ __forceinline__ void mtri_sums(const Pair<R> *__restrict__ pair, const int32_t *__restrict__ mp_off,
+                                          const int32_t *__restrict__ mp_list, const R *__restrict__ tri_nrm,
+                                          int64_t Tm, const DevStatus *st, int64_t cap_pairs, R *__restrict__ mtri,
+                                          unsigned blk) {
+  const int64_t gt = (int64_t)blk * NT + threadIdx.x;
   const int64_t t = gt >> 2;
   const int sub = (int)(gt & 3);
   const bool live = t < Tm && (int64_t)st->n_pairs <= cap_pairs;
@@ -1301,6 +1300,15 @@ __global__ __launch_bounds__(kThreads) void k_mtri(const Pair<R> *__restrict__ p
   R *out = mtri + 45 * t;
   for (int z = 0; z < 36; ++z) out[z] = h[z];
   for (int z = 0; z < 9; ++z) out[36 + z] = g[z];
+}
+
+template <typename R>
+__global__ __launch_bounds__(kThreads) void k_mtri(const Pair<R> *__restrict__ pair,
+                                                    const int32_t *__restrict__ mp_off,
+                                                    const int32_t *__restrict__ mp_list,
+                                                    const R *__restrict__ tri_nrm, int64_t Tm, const DevStatus *st,
+                                                    int64_t cap_pairs, R *__restrict__ mtri) {
+  mtri_sums<R, kThreads>(pair, mp_off, mp_list, tri_nrm, Tm, st, cap_pairs, mtri, blockIdx.x);
 }
 
 // Energy of environment e from its tiles: a fixed split over 1024 partial
@@ -1500,8 +1508,8 @@ constexpr size_t row_lds_wave(int slots, int pass, bool heavy, int light_bound) 
 // HEAVY: the heavy rows (large LDS tables), without a.split all rows, same code;
 // rlist / rcount: the light rows' list, and a.V entries on the heavy rows'
 template <typename R, int PASS, bool HEAVY>
-__global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slots, const int4 *__restrict__ rlist,
-                                                           const int32_t *__restrict__ rcount) {
+__device__ __forceinline__ void rows_walk(const RowArgs<R> &a, int slots, const int4 *__restrict__ rlist,
+                                          const int32_t *__restrict__ rcount, const int blk, const int nblk) {
   constexpr int pass = PASS;
   extern __shared__ __align__(16) unsigned char smem[];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
@@ -1524,7 +1532,7 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
   uint16_t *smap = reinterpret_cast<uint16_t *>(snrm + 3 * kRowSrc);  // place in `dense` of a slot's column
   if (pass == 1 || pass == 3) {
     const int64_t nnzb = a.row_ptr[a.V];
-    if (pass == 1 && HEAVY != a.split && blockIdx.x == 0 && threadIdx.x == 0) {  // the BSR's block count
+    if (pass == 1 && HEAVY != a.split && blk == 0 && threadIdx.x == 0) {  // the BSR's block count
       a.st->nnzb = (unsigned long long)nnzb;
       if (nnzb > a.cap_nnzb) atomicCAS(&a.st->code, 0, GMCP_E_CAPACITY);
     }
@@ -1557,13 +1565,13 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
   // rows in dispatch order: an XCD-by-XCD mapping of the list measured
   // several times slower (the rows with work cluster in the list, so the
   // XCDs holding them finish last)
-  const int lblk = blockIdx.x;
+  const int lblk = blk;
   // each list entry carries the row's adjacency range and contribution
   // count (k_row_pre), so a row starts with one load.  The loads are
   // pipelined over the wave's rows: the entry two rows ahead and the first
   // adjacency entries (one per lane) of the next row are in flight while the
   // wave works on the current one.
-  const int64_t lstride = (int64_t)gridDim.x * nw;
+  const int64_t lstride = (int64_t)nblk * nw;
   int64_t li = (int64_t)lblk * nw + w;
   auto first_ent = [&](const int4 r) -> int {  // adjacency entry sb + lane of row r
     if (pass == 3 || r.y + lane >= r.z) return 0;
@@ -1983,6 +1991,27 @@ __global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slo
     ent_c = ent_n;
     rr_n = rr_nn;
   }
+}
+
+template <typename R, int PASS, bool HEAVY>
+__global__ __launch_bounds__(kWave *kRowWaves) void k_rows(RowArgs<R> a, int slots, const int4 *__restrict__ rlist,
+                                                           const int32_t *__restrict__ rcount) {
+  rows_walk<R, PASS, HEAVY>(a, slots, rlist, rcount, blockIdx.x, gridDim.x);
+}
+
+// Few rows: the count of all of them and, in blocks of its own, the
+// master-triangle sums, which the count does not wait for (a launch less in
+// a small step's chain)
+template <typename R>
+__global__ __launch_bounds__(kWave *kHeavyWaves) void k_rows_sums(RowArgs<R> a, int slots,
+                                                                  const int4 *__restrict__ rlist,
+                                                                  const int32_t *__restrict__ rcount, int row_blocks,
+                                                                  int64_t Tm, R *__restrict__ mtri) {
+  if ((int)blockIdx.x < row_blocks)
+    rows_walk<R, 0, true>(a, slots, rlist, rcount, blockIdx.x, row_blocks);
+  else
+    mtri_sums<R, kWave * kHeavyWaves>(a.pair, a.mp_off, a.mp_list, a.tri_nrm, Tm, a.st_r, a.cap_pairs, mtri,
+                                      blockIdx.x - row_blocks);
 }
 
 
@@ -2451,13 +2480,19 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
       return (size_t)(heavy ? kHeavyWaves : nw) * row_lds_wave<R>(sl, pass, heavy, ra.light_bound);
     };
     if ((e = fork()) != hipSuccess) return e;
+    const bool count_sums = !ra.split && sums && !c->prof.on;
     prof_mark(c, ST_ROWS_COUNT_H, 0);
-    hipLaunchKernelGGL((k_rows<R, 0, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 0, true), hs, ra, hslots,
-                       b.rlist, b.rcount);
+    if (count_sums)
+      hipLaunchKernelGGL(k_rows_sums<R>, dim3(hgrid.x + nblk(4 * c->Tm, kWave * kHeavyWaves)),
+                         dim3(kWave * kHeavyWaves), lds(hslots, 0, true), s, ra, hslots, b.rlist, b.rcount,
+                         (int)hgrid.x, c->Tm, (R *)b.mtri);
+    else
+      hipLaunchKernelGGL((k_rows<R, 0, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 0, true), hs, ra, hslots,
+                         b.rlist, b.rcount);
     prof_mark(c, ST_ROWS_COUNT_H, 1);
     if ((e = mark_side()) != hipSuccess) return e;
     if (rank_beside) rank_on(hs);
-    if (sums) mtri(hs);  // read by the writing pass, beside the scan
+    if (sums && !count_sums) mtri(hs);  // read by the writing pass, beside the scan
     prof_mark(c, ST_ROWS_COUNT, 0);
     if (ra.split)
       hipLaunchKernelGGL((k_rows<R, 0, false>), rgrid, dim3(kWave * nw), lds(lslots, 0, false), s, ra, lslots, b.rlist,
