@@ -18,15 +18,6 @@ constexpr int kScanTile = kScanThreads * kScanPer;  // 16384 elements per tile
 // was corrupted; the kernel then reports an error instead of waiting on
 constexpr int kScanSpin = 1 << 20;
 
-__device__ inline int wave_incl_scan(int v, int lane) {
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    int t = __shfl_up(v, d, kWave);
-    if (lane >= d) v += t;
-  }
-  return v;
-}
-
 // Tile descriptors of the single-pass scan: epoch (30 bits, the call) |
 // state (2 bits: 1 = the tile's own sum, 2 = its inclusive prefix) | value.
 // A descriptor of another epoch reads as "not yet published".
@@ -66,18 +57,19 @@ __device__ inline bool scan_tile_used(int64_t t0, int64_t t1, int64_t n, const G
   return false;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_lookback(const int32_t *__restrict__ in,
-                                                                int32_t *__restrict__ out, int64_t n,
-                                                                int64_t ntiles, unsigned long long *ticket,
-                                                                unsigned long long *desc, DevStatus *st,
-                                                                const GridEnv *__restrict__ grid,
-                                                                const EnvInfo *__restrict__ env, int n_env) {
+__device__ __forceinline__ void scan_body(const int32_t *__restrict__ in, int32_t *__restrict__ out, int64_t n,
+                                          int64_t ntiles, unsigned long long *ticket, unsigned long long *desc,
+                                          DevStatus *st, const GridEnv *__restrict__ grid,
+                                          const EnvInfo *__restrict__ env, int n_env) {
   __shared__ uint32_t s_tile, s_epoch;
   __shared__ int s_used;
   __shared__ int wsum[kScanPer / 4][kScanThreads / kWave];
+  static_assert(sizeof(wsum) == kWave * sizeof(int), "a wave scans the sums");
   __shared__ int lb_first[kScanThreads / kWave], lb_wait[kScanThreads / kWave], lb_sum[kScanThreads / kWave];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  if (tid == 0) {
+  // one tile: no ticket, no descriptors (a round trip and a barrier less)
+  const bool alone = ntiles == 1;
+  if (!alone && tid == 0) {
     const unsigned long long tk = atomicAdd(ticket, 1ull);
     const uint32_t t = (uint32_t)(tk & 0xffffffffull);
     if ((int64_t)t == ntiles - 1) atomicAdd(ticket, (1ull << 32) - (unsigned long long)ntiles);
@@ -86,14 +78,14 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_lookback(const int32_t *_
     s_used = (int64_t)t >= ntiles || !grid ||
              scan_tile_used((int64_t)t * kScanTile, ((int64_t)t + 1) * kScanTile, n, grid, env, n_env);
   }
-  __syncthreads();
-  const int64_t tile = (int64_t)s_tile;  // 0 .. 2^32 - 1
+  if (!alone) __syncthreads();
+  const int64_t tile = alone ? 0 : (int64_t)s_tile;  // 0 .. 2^32 - 1
   if (tile >= ntiles) {  // only if the ticket word was corrupted: no descriptor to write
     if (tid == 0) set_error(st, GMCP_E_TIMEOUT, (unsigned long long)tile);
     return;
   }
-  const uint32_t epoch = s_epoch;
-  if (!s_used) {  // unused cells: a zero sum (tile 0: its prefix), nothing loaded or written
+  const uint32_t epoch = alone ? 0 : s_epoch;
+  if (!alone && !s_used) {  // unused cells: a zero sum (tile 0: its prefix), nothing loaded or written
     if (tid == 0)
       __hip_atomic_store(&desc[tile], scan_desc(epoch, tile == 0 ? 2u : 1u, 0), __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
@@ -116,21 +108,19 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_lookback(const int32_t *_
       q[k].w = 0;
     }
     gs[k] = q[k].x + q[k].y + q[k].z + q[k].w;
-    gi[k] = wave_incl_scan(gs[k], lane);
+    gi[k] = wave_incl_add(gs[k]);
     if (lane == kWave - 1) wsum[k][w] = gi[k];
   }
   __syncthreads();
-  // offset of (group k, wave w) in the tile, and the tile's sum
-  int goff[kGroups], agg = 0;
+  // offset of (group k, wave w) in the tile, and the tile's sum: every wave
+  // scans the 64 sums (group-major) in its lanes
+  int goff[kGroups];
+  const int ws = (&wsum[0][0])[lane], wi = wave_incl_add(ws), wu = __builtin_amdgcn_readfirstlane(w);
+  const int agg = __builtin_amdgcn_readlane(wi, kWave - 1);
 #pragma unroll
-  for (int k = 0; k < kGroups; ++k) {
-    goff[k] = agg;
-    for (int i = 0; i < kScanThreads / kWave; ++i) {
-      if (i < w) goff[k] += wsum[k][i];
-      agg += wsum[k][i];
-    }
-  }
-  if (tid == 0)
+  for (int k = 0; k < kGroups; ++k)
+    goff[k] = __builtin_amdgcn_readlane(wi - ws, k * (kScanThreads / kWave) + wu);
+  if (!alone && tid == 0)
     __hip_atomic_store(&desc[tile], scan_desc(epoch, tile == 0 ? 2u : 1u, agg), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
   // look back over windows of kScanThreads predecessors (thread k reads
@@ -197,6 +187,27 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_lookback(const int32_t *_
   }
 }
 
+__global__ __launch_bounds__(kScanThreads) void k_scan_lookback(const int32_t *__restrict__ in,
+                                                                int32_t *__restrict__ out, int64_t n,
+                                                                int64_t ntiles, unsigned long long *ticket,
+                                                                unsigned long long *desc, DevStatus *st,
+                                                                const GridEnv *__restrict__ grid,
+                                                                const EnvInfo *__restrict__ env, int n_env) {
+  scan_body(in, out, n, ntiles, ticket, desc, st, grid, env, n_env);
+}
+
+// Long scans (a batch's grid cells), one block per CU: the swept grid's scan
+// on the second stream then starts where the narrow phase's blocks have left
+// the CUs, instead of slowing them (256 environments, step: 4.74 ms, with two
+// blocks per CU 4.83).
+constexpr int64_t kScanLong = 256;  // tiles (4 M elements)
+__global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_scan_long(
+    const int32_t *__restrict__ in, int32_t *__restrict__ out, int64_t n, int64_t ntiles, unsigned long long *ticket,
+    unsigned long long *desc, DevStatus *st, const GridEnv *__restrict__ grid, const EnvInfo *__restrict__ env,
+    int n_env) {
+  scan_body(in, out, n, ntiles, ticket, desc, st, grid, env, n_env);
+}
+
 __global__ void k_fill_i32(int32_t *p, int32_t v, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -240,7 +251,7 @@ hipError_t scan_exclusive(gmcp_ctx *c, const int32_t *in, int32_t *out, int64_t 
       ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15))
     return hipErrorInvalidValue;
   unsigned long long *ticket = reinterpret_cast<unsigned long long *>(scratch);
-  hipLaunchKernelGGL(k_scan_lookback, dim3((unsigned)ntiles), dim3(kScanThreads), 0, c->stream, in, out, n, ntiles,
+  hipLaunchKernelGGL(ntiles > kScanLong ? k_scan_long : k_scan_lookback, dim3((unsigned)ntiles), dim3(kScanThreads), 0, c->stream, in, out, n, ntiles,
                      ticket, ticket + 1, c->b.status, grid, c->b.env, c->n_env);
   return hipGetLastError();
 }

@@ -1,6 +1,7 @@
 """The two launch shapes of the BSR row kernels (Sec. 4.2 Hessian scatter):
 one launch over light and heavy rows below 16384 rows, separate launches from
-there on.  A pad under a punch of coarse triangles (light slave rows, heavy
+there on.  The scan of the row counts crosses from one tile of 16384 entries
+to two at the same place.  A pad under a punch of coarse triangles (light slave rows, heavy
 master rows) just below and just above the line, full and kinematic, against
 the oracle; the gradient-only assembly takes the same lists and must repeat
 the gradient.  Tolerances are those of the other comparisons with the oracle."""
