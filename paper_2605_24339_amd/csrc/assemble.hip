@@ -2402,12 +2402,12 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   hipLaunchKernelGGL(k_pair_bucket<R>, dim3(pb), dim3(kThreads), 0, s, pr, b.status, c->caps.pairs, b.mp_cnt,
                      b.mp_off, b.mp_key, c->Tm);
   const RankArgs<R> rank{pr, b.mp_off, b.mp_key, b.mp_list, b.status, c->caps.pairs};
-  // The order inside the buckets is read by the master-triangle sums: before
-  // the rows of a gradient alone, beside the row counts on the second stream
-  // where the rows are split, else in the row lists' launch
-  const bool split = c->V >= kSplitRows, rank_first = !H || !c->V, rank_beside = !rank_first && split;
-  auto rank_on = [&](hipStream_t st) { hipLaunchKernelGGL(k_bucket_rank<R>, dim3(pb), dim3(kThreads), 0, st, rank); };
-  if (rank_first) rank_on(s);
+  // The order inside the buckets is read by the master-triangle sums: found
+  // before the rows of a gradient alone, else in the row lists' launch (beside
+  // the row counts on the second stream it held the sums there: large
+  // indentation 219.5 against 218 us, clipped samples 327.5 and 323)
+  const bool rank_first = !H || !c->V;
+  if (rank_first) hipLaunchKernelGGL(k_bucket_rank<R>, dim3(pb), dim3(kThreads), 0, s, rank);
   prof_mark(c, ST_BUCKET, 1);
   RowArgs<R> ra = row_args<R>(c, H);
   ra.grad = grad;
@@ -2419,7 +2419,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   // lists; a fork and its join cost more than a row kernel takes there.
   // One launch against two (step): 931 rows 185 and 292 us (enqueued one by
   // one), 9136 rows 165 and 177, 36893 rows 242 and 229.
-  ra.split = split;
+  ra.split = c->V >= kSplitRows;
   const bool par = ra.split && c->side != nullptr && !c->prof.on;
   const hipStream_t hs = par ? c->side : s;
   auto fork = [&]() {
@@ -2442,8 +2442,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   };
   if (sums && !H) mtri(s);  // the gradient rows read the sums
   const unsigned rank_blocks =
-      rank_first || rank_beside ? 0
-                                : (unsigned)std::min<int64_t>(nblk(c->caps.pairs, kPreThreads), kPairBlocks / 2);
+      rank_first ? 0 : (unsigned)std::min<int64_t>(nblk(c->caps.pairs, kPreThreads), kPairBlocks / 2);
   const EnergyArgs<R> en{b.tile_E, b.tile_act, b.epoch, b.env, energy, c->mortar};
   if (grad || H) {
     prof_mark(c, ST_ROWS_PRE, 0);
@@ -2491,7 +2490,6 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
                          b.rlist, b.rcount);
     prof_mark(c, ST_ROWS_COUNT_H, 1);
     if ((e = mark_side()) != hipSuccess) return e;
-    if (rank_beside) rank_on(hs);
     if (sums && !count_sums) mtri(hs);  // read by the writing pass, beside the scan
     prof_mark(c, ST_ROWS_COUNT, 0);
     if (ra.split)
@@ -2502,7 +2500,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     e = scan_exclusive(c, b.row_cnt, H->row_ptr, c->V + 1);
     if (e != hipSuccess) return e;
     if ((e = fork()) != hipSuccess) return e;
-    if ((e = join()) != hipSuccess) return e;  // the sums
+    if (sums && (e = join()) != hipSuccess) return e;  // the sums
     prof_mark(c, ST_ROWS_FILL_H, 0);
     hipLaunchKernelGGL((k_rows<R, 1, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 1, true), hs, ra, hslots,
                        b.rlist, b.rcount);
