@@ -1186,6 +1186,8 @@ constexpr int kRowWaves = 2;   // light rows
 // environments, step: 5.97 ms, with half as many 5.71)
 constexpr int kHeavyWaves = 1;
 constexpr int64_t kSplitRows = 16384;  // rows from which light and heavy ones are launched apart
+constexpr int64_t kRankBeside = int64_t(1) << 21;  // rows from which the buckets' order has a launch beside the counts
+static_assert(kRankBeside >= kSplitRows, "the second stream is the split rows'");
 // the list-walking row kernels use fixed grids, by default many times the
 // blocks resident at once (kDefaultRowBlocks light, kDefaultHeavyBlocks
 // heavy): a block's share of the list is short, so blocks that start late
@@ -2403,11 +2405,14 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
                      b.mp_off, b.mp_key, c->Tm);
   const RankArgs<R> rank{pr, b.mp_off, b.mp_key, b.mp_list, b.status, c->caps.pairs};
   // The order inside the buckets is read by the master-triangle sums: found
-  // before the rows of a gradient alone, else in the row lists' launch (beside
-  // the row counts on the second stream it held the sums there: large
-  // indentation 219.5 against 218 us, clipped samples 327.5 and 323)
-  const bool rank_first = !H || !c->V;
-  if (rank_first) hipLaunchKernelGGL(k_bucket_rank<R>, dim3(pb), dim3(kThreads), 0, s, rank);
+  // before the rows of a gradient alone, else in the row lists' launch, for
+  // millions of rows beside the row counts on the second stream.  In that
+  // launch against beside the counts (step): 36893 rows 218 and 219.5 us, with
+  // clipped samples 323 and 327.5; 1.96 M rows 2237 and 2261; 3.9 M rows 4670
+  // both, with light rows up to 256 entries 4640 and 4580.
+  const bool rank_first = !H || !c->V, rank_beside = !rank_first && c->V >= kRankBeside;
+  auto rank_on = [&](hipStream_t st) { hipLaunchKernelGGL(k_bucket_rank<R>, dim3(pb), dim3(kThreads), 0, st, rank); };
+  if (rank_first) rank_on(s);
   prof_mark(c, ST_BUCKET, 1);
   RowArgs<R> ra = row_args<R>(c, H);
   ra.grad = grad;
@@ -2442,7 +2447,8 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
   };
   if (sums && !H) mtri(s);  // the gradient rows read the sums
   const unsigned rank_blocks =
-      rank_first ? 0 : (unsigned)std::min<int64_t>(nblk(c->caps.pairs, kPreThreads), kPairBlocks / 2);
+      rank_first || rank_beside ? 0
+                                : (unsigned)std::min<int64_t>(nblk(c->caps.pairs, kPreThreads), kPairBlocks / 2);
   const EnergyArgs<R> en{b.tile_E, b.tile_act, b.epoch, b.env, energy, c->mortar};
   if (grad || H) {
     prof_mark(c, ST_ROWS_PRE, 0);
@@ -2490,6 +2496,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
                          b.rlist, b.rcount);
     prof_mark(c, ST_ROWS_COUNT_H, 1);
     if ((e = mark_side()) != hipSuccess) return e;
+    if (rank_beside) rank_on(hs);
     if (sums && !count_sums) mtri(hs);  // read by the writing pass, beside the scan
     prof_mark(c, ST_ROWS_COUNT, 0);
     if (ra.split)
@@ -2500,7 +2507,7 @@ hipError_t launch_assemble(gmcp_ctx *c, const R *xs, const R *xm, const R *g_ref
     e = scan_exclusive(c, b.row_cnt, H->row_ptr, c->V + 1);
     if (e != hipSuccess) return e;
     if ((e = fork()) != hipSuccess) return e;
-    if (sums && (e = join()) != hipSuccess) return e;  // the sums
+    if ((sums || rank_beside) && (e = join()) != hipSuccess) return e;  // the sums
     prof_mark(c, ST_ROWS_FILL_H, 0);
     hipLaunchKernelGGL((k_rows<R, 1, true>), hgrid, dim3(kWave * kHeavyWaves), lds(hslots, 1, true), hs, ra, hslots,
                        b.rlist, b.rcount);
